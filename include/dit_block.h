@@ -230,13 +230,14 @@ dit_status dit_linear(const void *a, int64_t lda, const void *w, int64_t ldw,
                       int64_t gate_stride, const int32_t *cu_seqlens, int n_req,
                       dit_dtype dtype, hipStream_t stream);
 
-/* The bf16 GEMM computes 256 x 256 output tiles, or 256 x 192 where fewer
- * rounds of tiles over the compute units make that faster (shapes with few
- * tiles).  For tests and tuning: tile_n = 192 or 256 forces that width for
- * every later bf16 GEMM of this process (every entry point), 0 restores the
- * choice per shape; any other value gives DIT_ERR_INVALID_ARG.  Results do
- * not depend on the width.  Process-wide setting; not synchronised with work
- * in flight (set it between calls). */
+/* The bf16 GEMM computes 256 x 256 output tiles, or smaller ones (256 x 192,
+ * 128 x 256, 128 x 192, 128 x 128) where the rounds of tiles over the compute
+ * units then take less time (few rows).  For tests and tuning: tile_n = 192
+ * or 256 forces 256-row tiles of that width for every later bf16 GEMM of this
+ * process (every entry point), 0 restores the choice per shape; any other
+ * value gives DIT_ERR_INVALID_ARG.  Results do not depend on the tile shape.
+ * Process-wide setting; not synchronised with work in flight (set it between
+ * calls). */
 dit_status dit_debug_gemm_tile_n(int tile_n);
 
 /* The bf16 self-attention (key ranges over 1024) runs its work items in

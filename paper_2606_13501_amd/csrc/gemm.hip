@@ -1,24 +1,48 @@
 // Projections of the DiT block: out = epilogue(A . W^T + bias).
 //
-// bf16: a 256x256 (or 256x192) output tile per 256-thread workgroup on the
-// gfx950 matrix cores (v_mfma_f32_32x32x16_bf16), fp32 accumulation.  Each of
-// the 4 waves (one per SIMD) owns a 128x128 (128x96) sub-tile whose
-// accumulators (256 or 192 registers) live in the accumulation registers.  The K loop runs in steps of 64: a
-// step's operand tiles are 256 rows x 128 B, i.e. whole cache lines per row.
-// LDS double-buffers two steps (2 x 64 KiB); two register stages carry the
-// next two steps from global memory, so a load has about two steps of MFMA
-// work to land.  Global loads, LDS stores and fragment reads are spread
-// evenly between the MFMAs (the memory pipeline never sees a burst that
-// would stall MFMA issue).  The 16-byte chunks of each 128-byte LDS row are
-// XOR-swizzled so fragment reads are free of bank conflicts.  The kernel
-// computes C^T blocks (W as the MFMA A operand) so that every lane ends up
-// holding four consecutive output columns of one row, stored as one 8-byte
-// write with the fused epilogue (bias, GELU-tanh, residual, gated residual).
-// Workgroups are rastered in groups of 2 tile rows per XCD so the tiles
-// resident on one XCD share A and W panels in its L2.
+// bf16: one 256-thread workgroup per compute unit runs a sequence of output
+// tiles on the gfx950 matrix cores, fp32 accumulation.  Each of the 4 waves
+// (one per SIMD) owns a quarter of the tile, at most 128 x 128, whose
+// accumulators live in the accumulation registers.
+//
+// The matrix instruction is v_mfma_f32_16x16x32_bf16.  These kernels run at
+// the board's power limit, and with random operands this shape sustains
+// 2.03-2.05 PFLOP/s on the whole chip where v_mfma_f32_32x32x16_bf16 sustains
+// 1.78 (register-only loops, 256 x 4 waves; with zeros both reach 2.4).  The
+// QKV projection at 75,600 x 15,360 x 5,120 went from 8.9 to 8.4 ms with the
+// instruction alone.
+//
+// The K loop runs in steps of 64: a step's operand tiles are rows of 128 B,
+// i.e. whole cache lines.  They go straight from global memory into LDS
+// (buffer loads with the lds modifier), into two rings of slots, one per
+// operand: no staging registers and no LDS stores, so the loop is 128 MFMAs,
+// 32 fragment reads and 16 loads per step for a 256 x 256 tile.  One operand
+// (X) has R slots and the other (Y) R + 1: that fills the 160 KiB of LDS with
+// 256 x 256 tiles (R = 2) and keeps 1.5 to 2 steps in flight.  A step is two
+// halves of 32 in K.  During the MFMAs of a half, the fragments of the next
+// half are read; at the barrier between the halves of step s every wave has
+// read all of step s and the loads of step s + 1 have landed, so the slot of
+// X(s) is refilled with X(s + R) right after it, and the slot of Y(s) with
+// Y(s + R + 1) in the first half of step s + 1.  The load cursor runs on into
+// the workgroup's next tile, which therefore starts with its first steps in
+// LDS; past the last tile it loads nothing (an empty descriptor).
+//
+// The 16-byte chunks of each 128-byte LDS row are XOR-swizzled so fragment
+// reads are free of bank conflicts.  The kernel computes C^T blocks (W as the
+// MFMA A operand) so that a lane holds four consecutive output columns of one
+// row.  Every tile shape adds up an output element in the same order (one
+// chain of 32-wide products, K ascending), so results do not depend on the
+// shape: a row of a packed batch has the same bits as alone.
+//
+// Measured against the former kernel (32x32x16, register-staged loads), the
+// builds timed in turn, with the fused epilogues: 75,600 x 15,360 x 5,120
+// 8.69 -> 8.28 ms (1.44 PFLOP/s); 4,096 x 12,288 x 3,072 (GELU) 257 -> 224
+// us; 4,096 x 3,072 x 12,288 246 -> 210 us; 4,096 x 9,216 x 3,072 189 -> 161
+// us; 1,024 x 3,072 x 3,072 63 -> 27 us; 1,024 x 3,072 x 12,288 171 -> 81 us.
 //
 // fp32: a plain 64x64 LDS-tiled FMA kernel for the small exact configuration.
 #include <atomic>
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -27,18 +51,10 @@ namespace dit {
 
 namespace {
 
-constexpr int BM = 256, BK = 64;               // tile rows, K step (columns: 256 or 192)
-constexpr int kWaves = 4;                           // 2 x 2 waves, each a 128 x 128 sub-tile
+constexpr int BK = 64;                              // K step
+constexpr int kWaves = 4;                           // 2 x 2 waves
 constexpr int kThreads = 64 * kWaves;
-constexpr int kStages = 2;                          // LDS double buffer
 constexpr int kRowBytes = BK * 2;                   // 128 B: one full cache line per tile row
-constexpr int kTileBytes = BM * kRowBytes;          // one operand tile of one step (32 KiB)
-constexpr int kStageBytes = 2 * kTileBytes;         // A tile + W tile
-constexpr int kLoads = kTileBytes / 1024 / kWaves;  // 1 KiB loads per wave, operand and step (8)
-constexpr int kEpiBytes = 32 * 256;                 // per wave: 32 rows x 64 fp32 (epilogue window)
-constexpr int kGroupM = 2;                          // tile rows per raster group
-constexpr int kGroupMFew = 8;                       // the same, at most kFewTileRows tile rows
-constexpr int kFewTileRows = 16;
 constexpr int kXcds = 8;                            // gfx950: 8 XCDs, workgroups dispatched round-robin
 
 // gelu_tanh(z) = z (1 + tanh u) / 2 = z / (1 + e^(-2u)), u = sqrt(2/pi) (z + 0.044715 z^3)
@@ -54,15 +70,7 @@ __device__ __forceinline__ float gelu_tanh(float z) {
 // tiles (the dispatcher places workgroup b on XCD b mod 8); the workgroups of
 // one XCD take its tiles round-robin, so at any time they work on adjacent
 // tiles.  Logical tiles are rastered in groups of group_m tile rows, so the
-// tiles resident on one XCD share A and W panels in its L2.  Two tile rows per
-// group measured best at 75,600 rows (1-2.5% over 4, 8 and 16): the weights
-// of one GEMM (at most 157 MB) stay in the 256 MB MALL, so reuse of the
-// activation rows is what saves memory traffic.  With at most 16 tile rows
-// (4,096 rows: one to three rounds of tiles), groups of 8 rows: an XCD's 32
-// resident tiles then cover 8 x 4 tiles instead of 2 x 16 and read a quarter
-// of the W columns per step.  Measured in alternating order on one box at
-// 4,096 rows: 0.2-0.8% faster with D = 3,072 (output, up and down
-// projections), the same on the QKV shape.
+// tiles resident on one XCD share A and W panels in its L2 (see raster()).
 struct TileSeq {
   int first, stride, count;   // logical tiles first + stride * it, it < count
   int tiles_m, tiles_n, group_m;
@@ -93,22 +101,16 @@ __device__ __forceinline__ TileSeq tile_seq(int b, int nb, int tiles_m, int tile
   return q;
 }
 
-// 16-byte chunk swizzle of a 128-byte LDS row: a fragment read touches 16
-// consecutive rows at one logical chunk; rows 2t and 2t + 1 lie in different
-// halves of a 256-byte bank window and the physical chunk c ^ t differs
-// between the 8 values of t, so the 16 reads hit 16 distinct bank groups.
+// 16-byte chunk swizzle of a 128-byte LDS row: the 16 lanes that read 16
+// consecutive rows at one logical chunk touch, with rows 2t and 2t + 1 in
+// different halves of a 256-byte bank window and the physical chunk c ^ t
+// different for the 8 values of t, 16 distinct bank groups.
 __device__ __forceinline__ int row_swizzle(int r) { return (r >> 1) & 7; }
 
 // Raw buffer descriptor over `bytes` bytes from `base`.  The hardware's range
 // check covers the lane offset only (not the scalar offset), so a load
 // returns zeros where its lane offset is past the end; the loads below carry
 // every row offset in the lane offset.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, int64_t bytes) {
-  const uint32_t n = bytes > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)(bytes < 0 ? 0 : bytes);
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)n, 0x00020000);
-}
-
-// The same descriptor as a plain vector (operand of the LDS-direct load).
 __device__ __forceinline__ u32x4 make_desc(const void* base, int64_t bytes) {
   const uint32_t n = bytes > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)(bytes < 0 ? 0 : bytes);
   const uint64_t p = (uint64_t)base;
@@ -121,417 +123,319 @@ __device__ __forceinline__ u32x4 make_desc(const void* base, int64_t bytes) {
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_lds16(const u32x4& desc, int voff, int soff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :: "s"(lds), "v"(voff), "s"(desc), "s"(soff) : "m0");
 }
 #pragma clang diagnostic pop
+template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 
-// SEQ: the workgroup runs a sequence of tiles (K / 64 even and >= 6);
-// otherwise one tile per workgroup and any K / 64.
-template <int EPI, bool SEQ, int BNT>
+// c += w . a^T for one 16 x 16 block, in place in the accumulation registers.
+// Inline assembly: where registers are left over, the compiler would give the
+// builtin's result other registers than its addend and copy the accumulators
+// back every step (110 -> 237 instructions per step, 82 -> 127 us at 1,024 x
+// 3,072 x 12,288).  The compiler does not see it as an MFMA, so the distances
+// to the vector instructions that write and read the accumulators are kept by
+// hand (the s_nop before and after the K loop).
+__device__ __forceinline__ void mfma16(f32x4& c, const bf16x8& w, const bf16x8& a) {
+  asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(a));
+}
+
+// A tile shape: each of the 2 x 2 waves owns MB x NB blocks of 16 x 16, the X
+// operand (A if XA, else W) has R ring slots and the other one R + 1.
+template <int MB_, int NB_, int R_, bool XA_>
+struct Shape {
+  static constexpr int MB = MB_, NB = NB_, RX = R_, RY = R_ + 1;
+  static constexpr bool XA = XA_;
+  static constexpr int BM = 32 * MB, BN = 32 * NB;
+  static constexpr int kSlotA = BM * kRowBytes, kSlotW = BN * kRowBytes;
+  static constexpr int RA = XA ? RX : RY, RW = XA ? RY : RX;
+  static constexpr int kBaseW = RA * kSlotA;                 // LDS: the ring of A, then the ring of W
+  static constexpr int kLds = kBaseW + RW * kSlotW;
+  static constexpr int LA = MB, LW = NB;                     // 1 KiB loads per wave and step
+  static constexpr int LX = XA ? LA : LW, LY = XA ? LW : LA;
+  static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
+};
+
+template <int EPI, typename S>
 __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_nt(
     const bf16* __restrict__ A, int64_t lda, const bf16* __restrict__ W, int64_t ldw,
     const bf16* __restrict__ bias, bf16* __restrict__ C, int64_t ldc, const bf16* R, int64_t ldr,
     const float* __restrict__ gate, int64_t gate_stride, ReqTable req, int M, int N, int K,
     int tiles_m, int tiles_n, int group_m, int plane_cols, int64_t plane_skip) {
-  constexpr int WN = BNT / 2;                    // columns of a wave's sub-tile
-  constexpr int NI = WN / 32;                    // its W blocks of 32 columns (4 or 3)
-  constexpr int kTileW = BNT * kRowBytes;        // the W tile of one step
-  constexpr int kStage = kTileBytes + kTileW;    // A tile, then W tile
-  constexpr int kLW = kTileW / 1024 / kWaves;    // 1 KiB W loads per wave and step (8 or 6)
-  __shared__ __attribute__((aligned(1024))) char smem[kStages * kStage + kWaves * kEpiBytes];
+  constexpr int MB = S::MB, NB = S::NB, BM = S::BM, BN = S::BN, RX = S::RX, RY = S::RY;
+  constexpr int LA = S::LA, LW = S::LW, LX = S::LX, LY = S::LY;
+  constexpr bool XA = S::XA;
+  __shared__ __attribute__((aligned(1024))) char smem[S::kLds];
 
   const TileSeq seq = tile_seq(blockIdx.x, gridDim.x, tiles_m, tiles_n, group_m);
   if (seq.count == 0) return;
-  int tm, tn;
-  seq.coords(0, tm, tn);
-  int m0 = tm * BM, n0 = tn * BNT;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
+  const int KT = K / BK;
 
-  // ---- global -> registers -> LDS.  A step's operand tile is 32 pieces of
-  // 1 KiB (8 rows x 128 B); wave w moves pieces q = 8 w .. 8 w + 7 of A and
+  // ---- global -> LDS.  A step's tile of an operand is pieces of 1 KiB (8
+  // rows x 128 B); wave w moves pieces LA w .. LA w + LA - 1 of A and LW w ..
   // of W.  Lane i of piece q holds row 8 q + i / 8, logical chunk
-  // (i % 8) ^ row_swizzle(row), and stores it at LDS byte q * 1024 + 16 i,
-  // i.e. physical chunk i % 8 of that row.
-  auto a_rs = make_rsrc(A + (int64_t)m0 * lda, ((int64_t)(M - m0 - 1) * lda + K) * 2);
-  auto w_rs = make_rsrc(W + (int64_t)n0 * ldw, ((int64_t)(N - n0 - 1) * ldw + K) * 2);
+  // (i % 8) ^ row_swizzle(row), and fills LDS byte 1024 q + 16 i of the slot.
   // Row 8 q + i / 8 has row_swizzle = 4 (q % 2) + i / 16, so the lane part of
   // a load's offset is one of two values per operand (by the parity of q)
-  // plus 8 q rows, a uniform value.
+  // plus a uniform number of rows; LA and LW are even, so the parity of q is
+  // that of u.  A load's lane offset is its row inside the tile and its chunk,
+  // the scalar offset the K step only: rows past the end of the operand (a
+  // ragged last tile) read as zeros and no load leaves the operand.
+  static_assert(LA % 2 == 0 && LW % 2 == 0, "the parity of a piece is that of its index in the wave");
   int a_vo[2], w_vo[2];
 #pragma unroll
   for (int par = 0; par < 2; ++par) {
     const int c = (lane & 7) ^ (4 * par + (lane >> 4));
-    a_vo[par] = (lane >> 3) * (int)lda * 2 + c * 16;
-    w_vo[par] = (lane >> 3) * (int)ldw * 2 + c * 16;
+    a_vo[par] = (LA * wave * 8 + (lane >> 3)) * (int)lda * 2 + c * 16;
+    w_vo[par] = (LW * wave * 8 + (lane >> 3)) * (int)ldw * 2 + c * 16;
   }
-  // A load's lane offset is its row inside the tile (piece row 8 q plus the
-  // lane's row i / 8) and its chunk; the scalar offset is the K step only.
-  // The descriptor's range check sees the whole row offset, so rows past the
-  // end of the operand (a ragged last tile) read as zeros and no load leaves
-  // the operand.  The piece part 8 q rows is uniform (a scalar added per
-  // load).  Steps past the last K step (prologue loads of a short K) reload
-  // the last one.
-  auto a_po = [&](int u) { return (kLoads * wave + u) * 16 * (int)lda; };   // 8 q rows, in bytes
-  auto w_po = [&](int u) { return (kLW * wave + u) * 16 * (int)ldw; };
-  auto k_off = [&](int step) { return min(step, K / BK - 1) * BK * 2; };
-  struct Stage { u32x4 a[kLoads], w[kLW]; };   // one step of this wave's pieces
-  auto gload = [&](Stage& r, int step) {
-    const int soff = k_off(step);
-#pragma unroll
-    for (int u = 0; u < kLoads; ++u) {
-      r.a[u] = __builtin_amdgcn_raw_buffer_load_b128(a_rs, a_vo[u & 1] + a_po(u), soff, 0);
-      if (u < kLW) r.w[u] = __builtin_amdgcn_raw_buffer_load_b128(w_rs, w_vo[u & 1] + w_po(u), soff, 0);
-    }
-  };
-  // LDS homes of this wave's pieces in the slot of `step`: A piece u, W piece u
-  auto a_home = [&](int step) { return smem + (step % kStages) * kStage + kLoads * wave * 1024 + lane * 16; };
-  auto w_home = [&](int step) {
-    return smem + (step % kStages) * kStage + kTileBytes + kLW * wave * 1024 + lane * 16;
-  };
-  auto sstore = [&](const Stage& r, int step) {
-    char* const sa = a_home(step);
-    char* const sw = w_home(step);
-#pragma unroll
-    for (int u = 0; u < kLoads; ++u) {
-      *reinterpret_cast<u32x4*>(sa + u * 1024) = r.a[u];
-      if (u < kLW) *reinterpret_cast<u32x4*>(sw + u * 1024) = r.w[u];
-    }
-  };
-
-  // ---- fragment reads: row base + 32 b + (lane & 31), logical chunk 2 kk + (lane >> 5)
-  const int fr = lane & 31;
-  const int fh = lane >> 5;
-  const int sw = row_swizzle(fr);   // == row_swizzle(base + 32 b + fr)
-  int fo_a[4], fo_w[4];             // + 32 * kRowBytes b
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    fo_a[kk] = (wm * 128 + fr) * kRowBytes + (((2 * kk + fh) ^ sw) << 4);
-    fo_w[kk] = kTileBytes + (wn * WN + fr) * kRowBytes + (((2 * kk + fh) ^ sw) << 4);
-  }
-  struct Frags { bf16x8 w[NI], a[4]; };
-  auto read = [&](Frags& f, int step, int kk) {
-    const char* st = smem + (step % kStages) * kStage;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) f.w[i] = *reinterpret_cast<const bf16x8*>(st + fo_w[kk] + i * 32 * kRowBytes);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) f.a[j] = *reinterpret_cast<const bf16x8*>(st + fo_a[kk] + j * 32 * kRowBytes);
-  };
-
-  // acc[i][j]: W block i (NI x 32 columns of the wave), A block j (4 x 32 rows)
-  f32x16 acc[NI][4];
-#pragma unroll
-  for (int i = 0; i < NI; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{};
-  auto mma = [&](const Frags& f) {
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[i], f.a[j], acc[i][j], 0, 0, 0);
-  };
-  const int KT = K / BK;
-  // Per K quarter: 16 MFMAs, the 8 fragment reads of the next quarter, and
-  // (when a register stage is being cycled) 4 LDS stores + 4 global loads.
-  // The reads go first, one per MFMA over the first half, so each has most
-  // of a quarter to land; the stores and loads are spread over the second
-  // half.  (Measured at 720p against reads, stores and loads interleaved
-  // evenly: QKV 8.85 against 9.16 ms; reads two per MFMA or loads before
-  // stores were no better.)  With 3 W blocks per wave: 12 MFMAs, 7 reads, up
-  // to 4 stores and 4 loads per quarter, in the same order.  Each quarter is
-  // closed by a scheduling fence (below), so the compiler cannot sink the
-  // next quarter's reads next to the MFMAs that consume them.
-  auto pattern = [] {
-    if constexpr (NI == 4) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {   // the next quarter's 8 reads, one per MFMA of the first half
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {   // stores and loads over the second half
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 7; ++i) {   // the next quarter's 7 reads, one per MFMA
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {   // stores and loads over the remaining MFMAs
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-      }
-    }
-  };
-
-
-  // items u0 .. u0 + 3 of a register stage (items 0-7: A pieces, 8-15: W
-  // pieces): store each into the LDS slot of step st_step, then reload it
-  // with step ld_step (each part only when asked for)
-  auto io4 = [&](Stage& R, int u0, int st_step, int ld_step, bool do_store, bool do_load) {
-    char* const sa = a_home(st_step);
-    char* const sw = w_home(st_step);
-    const int soff = ld_step * BK * 2;   // loads are asked for only while ld_step < K / 64
-#pragma unroll
-    for (int u = u0; u < u0 + 4; ++u) {
-      const int p = u & 7;
-      if (u < 8) {
-        if (do_store) *reinterpret_cast<u32x4*>(sa + p * 1024) = R.a[p];
-        if (do_load) R.a[p] = __builtin_amdgcn_raw_buffer_load_b128(a_rs, a_vo[p & 1] + a_po(p), soff, 0);
-      } else if (p < kLW) {
-        if (do_store) *reinterpret_cast<u32x4*>(sw + p * 1024) = R.w[p];
-        if (do_load) R.w[p] = __builtin_amdgcn_raw_buffer_load_b128(w_rs, w_vo[p & 1] + w_po(p), soff, 0);
-      }
-    }
-  };
-
-  // Pipeline.  LDS holds two steps (slots s % 2); each register stage holds
-  // one step in flight.  At the barrier in the middle of step s (before its
-  // last K quarter) every wave has finished reading slot s % 2, and the
-  // stores of step s + 1 into the other slot are complete.  From there the
-  // register stage of step s + 2 drains into slot s % 2 and refills with
-  // step s + 4, spread over the last quarter of step s and the first three
-  // of step s + 1; so a global load has about two steps to land.  Step s
-  // (f0 holds its quarter 0 on entry), with P the stage of window s - 1 and
-  // Q the stage of window s:
-  //   read q1 -> f1 | MFMAs f0 | P items 4-7      (store s + 1, load s + 3)
-  //   read q2 -> f0 | MFMAs f1 | P items 8-11
-  //   read q3 -> f1 | MFMAs f0 | P items 12-15
-  //   barrier
-  //   read q0 of s + 1 -> f0 | MFMAs f1 | Q items 0-3  (store s + 2, load s + 4)
-  // A workgroup runs a sequence of tiles.  The two LDS slots of a tile's
-  // last two steps are free after their mid-step barriers; the next tile's
-  // steps 0 and 1 are loaded straight into them from there (LDS-direct
-  // loads), so that tile starts without waiting for memory.  The last steps
-  // load nothing into the register stages, which are therefore free during
-  // the epilogue.  (With an odd step count the host gives every workgroup a
-  // single tile.)
+  const int a_pc = 16 * (int)lda, w_pc = 16 * (int)ldw;   // bytes of 8 rows
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
-  u32x4 nad{}, nwd{};   // the next tile's A and W
-  bool has_next = false;
-  auto dma_step = [&](int step) {   // step 0 or 1 of the next tile into slot `step` (K / 64 >= 6 here)
-    const uint32_t sa = lds_base + step * kStage + kLoads * wave * 1024;
-    const uint32_t sw = lds_base + step * kStage + kTileBytes + kLW * wave * 1024;
-    const int soff = step * BK * 2;
-#pragma unroll
-    for (int u = 0; u < kLoads; ++u) {
-      load_lds16(nad, a_vo[u & 1] + a_po(u), soff, sa + u * 1024);
-      if (u < kLW) load_lds16(nwd, w_vo[u & 1] + w_po(u), soff, sw + u * 1024);
+  // the load cursor: step l_step of the sequence's tile l_it
+  u32x4 ad{}, wd{};
+  int l_it = 0, l_step = 0;
+  auto set_tile = [&](int it) {
+    if (it < seq.count) {
+      int tm, tn;
+      seq.coords(it, tm, tn);
+      ad = make_desc(A + (int64_t)tm * BM * lda, ((int64_t)(M - tm * BM - 1) * lda + K) * 2);
+      wd = make_desc(W + (int64_t)tn * BN * ldw, ((int64_t)(N - tn * BN - 1) * ldw + K) * 2);
+    } else {   // past the last tile: empty ranges
+      ad[2] = 0;
+      wd[2] = 0;
     }
   };
-  Stage r0, r1;
-  Frags f0, f1;
-  // Step s: P drains step s + 1 (stP) and reloads with s + 3 (ldP), Q drains
-  // step s + 2 (stQ) and reloads with s + 4 (ldQ); `dma` >= 0 loads step dma
-  // of the next tile into slot dma after the barrier.  At the call sites the
-  // flags are constants wherever possible, so the compiler knows exactly
-  // which loads are in flight and derives exact wait counts.
-  auto step = [&](int s, Stage& P, Stage& Q, bool first, bool stP, bool ldP, bool stQ, bool ldQ, int dma) {
-    read(f1, s, 1);
-    mma(f0);
-    if (!first) io4(P, 4, s + 1, s + 3, stP, ldP);
-    pattern();
-    __builtin_amdgcn_sched_barrier(0);   // the quarter's reads stay in the quarter
-    read(f0, s, 2);
-    mma(f1);
-    if (!first) io4(P, 8, s + 1, s + 3, stP, ldP);
-    pattern();
-    __builtin_amdgcn_sched_barrier(0);   // the quarter's reads stay in the quarter
-    read(f1, s, 3);
-    mma(f0);
-    if (!first) io4(P, 12, s + 1, s + 3, stP, ldP);
-    pattern();
-    __builtin_amdgcn_sched_barrier(0);   // the quarter's reads stay in the quarter
-    __syncthreads();
-    if (dma >= 0) dma_step(dma);
-    read(f0, s + 1, 0);   // after the last step: a harmless read of the idle slot
-    mma(f1);
-    io4(Q, 0, s + 2, s + 4, stQ, ldQ);
-    pattern();
-    __builtin_amdgcn_sched_barrier(0);   // the quarter's reads stay in the quarter
+  auto advance = [&] {
+    if (++l_step == KT) {
+      l_step = 0;
+      set_tile(++l_it);
+    }
   };
-  // first tile: slots 0 and 1 get steps 0 and 1 through the register stages
-  // (with fewer K steps, steps past the end reload the last one; they fill
-  // slots and registers that are never consumed)
-  gload(r0, 0);
-  gload(r1, 1);
-  sstore(r0, 0);
-  sstore(r1, 1);
-  for (int it = 0;; ++it) {
-    has_next = SEQ && it + 1 < seq.count;
-    int tm1 = 0, tn1 = 0;
-    if (has_next) {
-      seq.coords(it + 1, tm1, tn1);
-      nad = make_desc(A + (int64_t)tm1 * BM * lda, ((int64_t)(M - tm1 * BM - 1) * lda + K) * 2);
-      nwd = make_desc(W + (int64_t)tn1 * BNT * ldw, ((int64_t)(N - tn1 * BNT - 1) * ldw + K) * 2);
-    }
-    // r0 / r1 carry steps 2 / 3; keep the two register stages' loads in this
-    // order (as in the loop), so the wait counts the compiler derives inside
-    // the loop stay exact
-    __builtin_amdgcn_sched_barrier(0);
-    gload(r0, 2);
-    __builtin_amdgcn_sched_barrier(0);
-    gload(r1, 3);
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();
-    read(f0, 0, 0);
-    // an even step uses (P, Q) = (r1, r0), an odd one (r0, r1); window -1
-    // (step 1 into slot 1) is already in LDS
-    if constexpr (SEQ) {
-      step(0, r1, r0, true, false, false, true, true, -1);
-      int s = 1;
-      for (; s + 5 < KT; s += 2) {
-        step(s, r0, r1, false, true, true, true, true, -1);
-        step(s + 1, r1, r0, false, true, true, true, true, -1);
-      }
-      // s = KT - 5: the last five steps, loads stop at step KT - 1
-      step(s, r0, r1, false, true, true, true, true, -1);
-      step(s + 1, r1, r0, false, true, true, true, false, -1);
-      step(s + 2, r0, r1, false, true, false, true, false, -1);
-      step(s + 3, r1, r0, false, true, false, false, false, has_next ? 0 : -1);
-      step(s + 4, r0, r1, false, false, false, false, false, has_next ? 1 : -1);
-    } else {   // any step count, a single tile
-      step(0, r1, r0, true, false, false, 2 < KT, 4 < KT, -1);
-      for (int s = 1; s < KT; s += 2) {
-        step(s, r0, r1, false, s + 1 < KT, s + 3 < KT, s + 2 < KT, s + 4 < KT, -1);
-        if (s + 1 < KT) step(s + 1, r1, r0, false, s + 2 < KT, s + 4 < KT, s + 3 < KT, s + 5 < KT, -1);
-      }
-    }
-    if (has_next) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the next tile's steps 0 and 1
+  auto load_a = [&](int u, int slot) {
+    load_lds16(ad, a_vo[u & 1] + u * a_pc, l_step * (BK * 2), lds_base + slot * S::kSlotA + (LA * wave + u) * 1024);
+  };
+  auto load_w = [&](int u, int slot) {
+    load_lds16(wd, w_vo[u & 1] + u * w_pc, l_step * (BK * 2),
+               lds_base + S::kBaseW + slot * S::kSlotW + (LW * wave + u) * 1024);
+  };
+  auto load_x = [&](int u, int slot) { if (XA) load_a(u, slot); else load_w(u, slot); };
+  auto load_y = [&](int u, int slot) { if (XA) load_w(u, slot); else load_a(u, slot); };
 
-  // Epilogue through a wave-private LDS window of 32 rows x 64 columns
-  // (fp32): acc[i][j][4 g + e] = C[m][n] with m = m0 + wm*128 + 32j + fr and
-  // n = n0 + wn*128 + 32i + 8g + 4fh + e.  Each round writes two column
-  // blocks of one row block as the MFMAs left them (a lane: 4 consecutive
-  // columns of one row) and reads them back row-contiguously, so each
-  // global access of a wave covers whole 128-byte row segments.  16-byte
-  // chunk c of window row r sits at physical chunk c ^ (r % 16): both the
-  // writes and the reads are free of bank conflicts.  One wave's LDS
-  // operations complete in order, so the window needs no barrier.
-  // The residual rows of two row blocks (and the gate row of each block,
-  // when all its rows belong to one request) are loaded before any of their
-  // outputs is computed, so the epilogue waits for memory twice per tile;
-  // the register stages are free here.  C may alias R: every element is
-  // read before it is written, by the same lane.
-  char* const ew = smem + kStages * kStage + wave * kEpiBytes;
-  const int er = lane >> 4, ec = lane & 15;   // read role: rows er + 4 k, chunk ec
-  float bsum[2][4];
-  int64_t c_off[2];   // output plane of the lane's 4 columns (planes: column n in plane n / plane_cols)
+  // ---- fragment reads: row base + 16 b + (lane & 15), logical chunk 4 kk + (lane >> 4) of half kk
+  const int fr = lane & 15, fh = lane >> 4;
+  const int sw = row_swizzle(fr);   // == row_swizzle(base + 16 b + fr)
+  int fo_a[2], fo_w[2];             // + 16 * kRowBytes b
 #pragma unroll
-  for (int ih = 0; ih < 2; ++ih) {
-    const int n = n0 + wn * WN + 64 * ih + 4 * ec;
-    c_off[ih] = plane_cols > 0 ? (int64_t)(n / plane_cols) * plane_skip : 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) bsum[ih][e] = 0.f;
-    if (bias && n < N && 64 * ih + 4 * ec < WN) {
-      const bf16x4 bv = *reinterpret_cast<const bf16x4*>(bias + n);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) bsum[ih][e] = (float)bv[e];
-    }
+  for (int kk = 0; kk < 2; ++kk) {
+    fo_a[kk] = (wm * 16 * MB + fr) * kRowBytes + (((4 * kk + fh) ^ sw) << 4);
+    fo_w[kk] = S::kBaseW + (wn * 16 * NB + fr) * kRowBytes + (((4 * kk + fh) ^ sw) << 4);
   }
+  struct Frags { bf16x8 w[NB], a[MB]; };
+  Frags f0, f1;
+  // acc[i][j][e] = C[m][n], m = 16 MB wm + 16 j + fr and n = 16 NB wn + 16 i + 4 fh + e of the tile
+  f32x4 acc[NB][MB];
+
+  // One half: the MFMAs on f, each followed by its share of the reads of the
+  // next half (half kk of the given slots) into g and of the loads, fenced so
+  // that the compiler keeps this order.  The reads go first, one per 2 MFMAs,
+  // so that each has half of the half to land.
+  constexpr int NM = MB * NB, NR = MB + NB;
+  constexpr int kReadStep = 2, kLoadStep = NM >= 48 ? 4 : 2;
+  static_assert((NM - 1) / kReadStep + 1 >= NR && (NM - 1) / kLoadStep + 1 >= (LX > LY ? LX : LY), "all reads and loads are issued");
+  auto half = [&](const Frags& f, Frags& g, int slot_x, int slot_y, int kk, auto loads_x, int load_slot) __attribute__((always_inline)) {
+    constexpr bool kX = decltype(loads_x)::value;
+    const char* const pa = smem + (XA ? slot_x : slot_y) * S::kSlotA + fo_a[kk];
+    const char* const pw = smem + (XA ? slot_y : slot_x) * S::kSlotW + fo_w[kk];
 #pragma unroll
-  for (int hj = 0; hj < 2; ++hj) {
+    for (int m = 0; m < NM; ++m) {
+      const int i = m / MB, j = m % MB;
+      mfma16(acc[i][j], f.w[i], f.a[j]);
+      const int r = m / kReadStep;   // reads in the order of their use: w0, a0 .., w1 ..
+      if (m % kReadStep == 0 && r < NR) {
+        if (r == 0) g.w[0] = *reinterpret_cast<const bf16x8*>(pw);
+        else if (r <= MB) g.a[r - 1] = *reinterpret_cast<const bf16x8*>(pa + (r - 1) * 16 * kRowBytes);
+        else g.w[r - MB] = *reinterpret_cast<const bf16x8*>(pw + (r - MB) * 16 * kRowBytes);
+      }
+      const int l = m / kLoadStep;
+      if (m % kLoadStep == 0 && l < (kX ? LX : LY)) {
+        if (kX) load_x(l, load_slot);
+        else load_y(l, load_slot);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  // the first tile's steps 0 .. R - 1, then the fragments of step 0's first half
+  set_tile(0);
+#pragma unroll
+  for (int s = 0; s < RX; ++s) {
+#pragma unroll
+    for (int u = 0; u < LX; ++u) load_x(u, s);
+#pragma unroll
+    for (int u = 0; u < LY; ++u) load_y(u, s);
+    advance();
+  }
+  wait_vmcnt<(RX - 1) * (LX + LY)>();
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NB; ++i) f0.w[i] = *reinterpret_cast<const bf16x8*>(smem + fo_w[0] + i * 16 * kRowBytes);
+#pragma unroll
+  for (int j = 0; j < MB; ++j) f0.a[j] = *reinterpret_cast<const bf16x8*>(smem + fo_a[0] + j * 16 * kRowBytes);
+  int sx = 0, sy = 0;   // slots of the current step, counted over all tiles: mod RX, mod RY
+  for (int it = 0; it < seq.count; ++it) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < MB; ++j) acc[i][j] = f32x4{};
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 1");   // a vector write of an MFMA's addend
+    __builtin_amdgcn_sched_barrier(0);
+    int tm, tn;
+    seq.coords(it, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    int last_y = 0;
+    for (int s = 0; s < KT; ++s) {
+      const int sx1 = sx == RX - 1 ? 0 : sx + 1;
+      const int sy1 = sy == RY - 1 ? 0 : sy + 1;
+      half(f0, f1, sx, sy, 1, std::false_type{}, sy == 0 ? RY - 1 : sy - 1);   // loads Y(s + R) into the slot of s - 1
+      // X(s + 1) and Y(s + 1) have landed; R - 2 steps of X and R - 1 of Y may still be in flight
+      wait_vmcnt<(RX - 2) * LX + (RX - 1) * LY>();
+      __syncthreads();
+      __builtin_amdgcn_sched_barrier(0);
+      half(f1, f0, sx1, sy1, 0, std::true_type{}, sx);                         // loads X(s + R) into the slot of s
+      advance();
+      last_y = sy;
+      sx = sx1;
+      sy = sy1;
+    }
+    // wait states from the last MFMA to a vector read of its result (the compiler itself would put at most 12)
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+
+    // Epilogue through a wave-private LDS window of 32 rows x CW columns
+    // (fp32), in the part of the last step's Y slot that this wave itself
+    // refills in the next step.  Each round writes the blocks of two row
+    // blocks as the MFMAs left them and reads them back row-contiguously,
+    // eight columns per lane, so each global access of a wave covers whole
+    // 64- or 128-byte row segments with 16 bytes per lane.  The window's 16-byte
+    // chunks are permuted (even chunks of a row first) and XOR-swizzled by row
+    // so that writes and reads are free of bank conflicts.  One wave's LDS
+    // operations complete in order, so the window needs no barrier.  The
+    // residual rows of a row block pair are loaded one pair ahead.  C may
+    // alias R: every element is read before it is written, by the same lane.
+    constexpr int CW = NB % 4 == 0 && LY >= 8 ? 64 : 32;   // the wave's share of a Y slot is LY KiB
+    constexpr int LPR = CW / 8, RPP = 64 / LPR;            // lanes per row and rows per pass when read back
+    constexpr int NP = 32 / RPP, NV = NB * 16 / CW;        // passes per window, windows per row block pair
+    static_assert(32 * CW * 4 <= LY * 1024 && NB * 16 % CW == 0 && MB % 2 == 0, "the window fits");
     constexpr bool kRes = EPI == DIT_EPI_RESIDUAL || EPI == DIT_EPI_GATED_RESIDUAL;
-    bf16x4 rv[2][2][8];
-    f32x4 gv[2][2];
-    bool g_one[2];
+    char* const ew = smem + (XA ? S::kBaseW + last_y * S::kSlotW : last_y * S::kSlotA) + wave * (LY * 1024);
+    const int er = lane / LPR, ec = lane % LPR;
+    auto at = [](int r, int c) {   // LDS byte of chunk c of window row r
+      if (CW == 64) return r * 256 + ((((c >> 1) | ((c & 1) << 3)) ^ (((r & 1) << 3) | ((r >> 1) & 7))) << 4);
+      return r * 128 + ((((c >> 1) | ((c & 1) << 2)) ^ ((((r >> 1) & 1) << 2) | ((r >> 2) & 3))) << 4);
+    };
+    const int nw = n0 + wn * 16 * NB + 8 * ec;   // the lane's first column of window 0
+    float bsum[NV][8];
+    int64_t c_off[NV];   // output plane of the lane's 8 columns (planes: column n in plane n / plane_cols)
 #pragma unroll
-    for (int jj = 0; jj < 2; ++jj) {
-      const int mb = m0 + wm * 128 + 32 * (2 * hj + jj);   // first row of the block
+    for (int v = 0; v < NV; ++v) {
+      const int n = nw + CW * v;
+      c_off[v] = plane_cols > 0 ? (int64_t)(n / plane_cols) * plane_skip : 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) bsum[v][e] = 0.f;
+      if (bias && n < N) {
+        const bf16x8 bv = *reinterpret_cast<const bf16x8*>(bias + n);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bsum[v][e] = (float)bv[e];
+      }
+    }
+    bf16x8 rv[2][NV][NP];
+    auto load_res = [&](int j) __attribute__((always_inline)) {
+      if constexpr (kRes) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+          for (int p = 0; p < NP; ++p) {
+            const int m = m0 + wm * 16 * MB + 32 * j + RPP * p + er, n = nw + CW * v;
+            rv[j & 1][v][p] = bf16x8{};
+            if (m < M && n < N) rv[j & 1][v][p] = *reinterpret_cast<const bf16x8*>(R + (int64_t)m * ldr + n);
+          }
+      }
+    };
+    load_res(0);
+#pragma unroll
+    for (int j = 0; j < MB / 2; ++j) {
+      if (j + 1 < MB / 2) load_res(j + 1);
+      const int mb = m0 + wm * 16 * MB + 32 * j;   // first row of the pair
+      f32x4 gv[NV][2];
+      bool g_one = true;                           // all rows of the pair belong to one request
       if (EPI == DIT_EPI_GATED_RESIDUAL) {
         const int r_lo = find_req(req.cu, req.n_req, min(mb, M - 1));
         const int r_hi = find_req(req.cu, req.n_req, min(mb + 31, M - 1));
-        g_one[jj] = r_lo == r_hi;
+        g_one = r_lo == r_hi;
 #pragma unroll
-        for (int ih = 0; ih < 2; ++ih) {
-          const int n = n0 + wn * WN + 64 * ih + 4 * ec;
-          gv[jj][ih] = f32x4{};
-          if (g_one[jj] && n < N && 64 * ih + 4 * ec < WN)
-            gv[jj][ih] = *reinterpret_cast<const f32x4*>(gate + (int64_t)r_lo * gate_stride + n);
-        }
-      }
-      if (kRes) {
-#pragma unroll
-        for (int ih = 0; ih < 2; ++ih) {
-          const int n = n0 + wn * WN + 64 * ih + 4 * ec;
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const int m = mb + 4 * k + er;
-            rv[jj][ih][k] = bf16x4{};
-            if (m < M && n < N && 64 * ih + 4 * ec < WN)
-              rv[jj][ih][k] = *reinterpret_cast<const bf16x4*>(R + (int64_t)m * ldr + n);
+        for (int v = 0; v < NV; ++v) {
+          gv[v][0] = gv[v][1] = f32x4{};
+          if (g_one && nw + CW * v < N) {
+            const float* gp = gate + (int64_t)r_lo * gate_stride + nw + CW * v;
+            gv[v][0] = *reinterpret_cast<const f32x4*>(gp);
+            gv[v][1] = *reinterpret_cast<const f32x4*>(gp + 4);
           }
         }
       }
-    }
 #pragma unroll
-    for (int jj = 0; jj < 2; ++jj) {
-      const int j = 2 * hj + jj;
+      for (int v = 0; v < NV; ++v) {
 #pragma unroll
-      for (int ih = 0; ih < 2; ++ih) {
+        for (int ii = 0; ii < CW / 16; ++ii)
 #pragma unroll
-        for (int ii = 0; ii < 2; ++ii) {
-          if (2 * ih + ii >= NI) continue;   // 3 W blocks: the last round holds one block (32 columns)
+          for (int jj = 0; jj < 2; ++jj)
+            *reinterpret_cast<f32x4*>(ew + at(16 * jj + fr, 4 * ii + fh)) = acc[v * (CW / 16) + ii][2 * j + jj];
+        const int n = nw + CW * v;
 #pragma unroll
-          for (int gq = 0; gq < 4; ++gq) {
-            const f32x4 v = {acc[2 * ih + ii][j][4 * gq], acc[2 * ih + ii][j][4 * gq + 1],
-                             acc[2 * ih + ii][j][4 * gq + 2], acc[2 * ih + ii][j][4 * gq + 3]};
-            const int c = 8 * ii + 2 * gq + fh;
-            *reinterpret_cast<f32x4*>(ew + fr * 256 + ((c ^ (fr & 15)) << 4)) = v;
-          }
-        }
-        const int n = n0 + wn * WN + 64 * ih + 4 * ec;
-        if (n >= N || 64 * ih + 4 * ec >= WN) continue;
+        for (int p = 0; p < NP; ++p) {
+          const int r = RPP * p + er, m = mb + r;
+          const f32x4 z0 = *reinterpret_cast<const f32x4*>(ew + at(r, 2 * ec));
+          const f32x4 z1 = *reinterpret_cast<const f32x4*>(ew + at(r, 2 * ec + 1));
+          float z[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int r = 4 * k + er;
-          const f32x4 zv = *reinterpret_cast<const f32x4*>(ew + r * 256 + ((ec ^ (r & 15)) << 4));
-          const int m = m0 + wm * 128 + 32 * j + r;
-          if (m >= M) continue;
-          float z[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) z[e] = zv[e] + bsum[ih][e];
+          for (int e = 0; e < 8; ++e) z[e] = (e < 4 ? z0[e & 3] : z1[e & 3]) + bsum[v][e];
           if (EPI == DIT_EPI_GELU_TANH) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) z[e] = gelu_tanh(z[e]);
+            for (int e = 0; e < 8; ++e) z[e] = gelu_tanh(z[e]);
           } else if (EPI == DIT_EPI_GATED_RESIDUAL) {
-            f32x4 g4 = gv[jj][ih];
-            if (!g_one[jj])   // the block spans a request boundary
-              g4 = *reinterpret_cast<const f32x4*>(gate + (int64_t)find_req(req.cu, req.n_req, m) * gate_stride + n);
+            f32x4 g0 = gv[v][0], g1 = gv[v][1];
+            if (!g_one && m < M && n < N) {   // the pair spans a request boundary
+              const float* gp = gate + (int64_t)find_req(req.cu, req.n_req, m) * gate_stride + n;
+              g0 = *reinterpret_cast<const f32x4*>(gp);
+              g1 = *reinterpret_cast<const f32x4*>(gp + 4);
+            }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) z[e] = (float)rv[jj][ih][k][e] + g4[e] * z[e];
+            for (int e = 0; e < 8; ++e) z[e] = (float)rv[j & 1][v][p][e] + (e < 4 ? g0[e & 3] : g1[e & 3]) * z[e];
           } else if (EPI == DIT_EPI_RESIDUAL) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) z[e] = (float)rv[jj][ih][k][e] + z[e];
+            for (int e = 0; e < 8; ++e) z[e] = (float)rv[j & 1][v][p][e] + z[e];
           }
-          bf16x4 o;
+          bf16x8 o;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = (bf16)z[e];
-          *reinterpret_cast<bf16x4*>(C + c_off[ih] + (int64_t)m * ldc + n) = o;
+          for (int e = 0; e < 8; ++e) o[e] = (bf16)z[e];
+          // computed on every path: were it left to the branch, a load above
+          // would be pending where the branch is not taken, and the compiler
+          // would wait for all loads in the K loop (90 -> 135 us at 1,024 x
+          // 3,072 x 12,288)
+          asm volatile("" : "+v"(o));
+          if (m < M && n < N) *reinterpret_cast<bf16x8*>(C + c_off[v] + (int64_t)m * ldc + n) = o;
         }
       }
     }
+    // the window's reads are done before the next step's loads overwrite it
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   }
-    if (!has_next) break;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{};
-    m0 = tm1 * BM;
-    n0 = tn1 * BNT;
-    a_rs = make_rsrc(A + (int64_t)m0 * lda, ((int64_t)(M - m0 - 1) * lda + K) * 2);
-    w_rs = make_rsrc(W + (int64_t)n0 * ldw, ((int64_t)(N - n0 - 1) * ldw + K) * 2);
-  }
+  wait_vmcnt<0>();   // no load may land in LDS after the workgroup has ended
 }
 
 // ----------------------------------------------------------------- fp32
@@ -595,44 +499,84 @@ __global__ __launch_bounds__(256) void gemm_f32_nt(
 
 std::atomic<int> g_tile_n{0};   // forced output tile width (0: chosen per shape)
 
-template <int EPI, int BNT>
-hipError_t launch_bf16_tiles(const LinearArgs& p, int tiles_m, int tiles_n, hipStream_t s) {
-  const int tiles = tiles_m * tiles_n;
-  int grid = (tiles + kXcds - 1) / kXcds * kXcds;   // one tile per workgroup
-  const int kt = p.K / BK;
-  const int group_m = tiles_m <= kFewTileRows ? kGroupMFew : kGroupM;
-  if (kt % 2 == 0 && kt >= 6) {
-    // one workgroup per compute unit, each running a sequence of tiles
-    const int resident = cu_count() / kXcds * kXcds;
-    if (resident >= kXcds && grid > resident) grid = resident;
-    gemm_bf16_nt<EPI, true, BNT><<<grid, kThreads, 0, s>>>(
-        (const bf16*)p.a, p.lda, (const bf16*)p.w, p.ldw, (const bf16*)p.bias, (bf16*)p.out, p.ldo,
-        (const bf16*)p.res, p.ldr, p.gate, p.gate_stride, p.req, (int)p.M, p.N, p.K, tiles_m, tiles_n,
-        group_m, p.plane_cols, p.plane_stride - p.plane_cols);
-  } else {
-    gemm_bf16_nt<EPI, false, BNT><<<grid, kThreads, 0, s>>>(
-        (const bf16*)p.a, p.lda, (const bf16*)p.w, p.ldw, (const bf16*)p.bias, (bf16*)p.out, p.ldo,
-        (const bf16*)p.res, p.ldr, p.gate, p.gate_stride, p.req, (int)p.M, p.N, p.K, tiles_m, tiles_n,
-        group_m, p.plane_cols, p.plane_stride - p.plane_cols);
+// The tile shapes, by the index of kCost.
+typedef Shape<8, 8, 2, false> Tile256x256;
+typedef Shape<8, 6, 2, false> Tile256x192;
+typedef Shape<4, 8, 2, true> Tile128x256;
+typedef Shape<4, 6, 3, false> Tile128x192;
+typedef Shape<4, 4, 4, false> Tile128x128;
+
+// What a launch of each shape takes on 256 compute units, in us: per round of
+// tiles (one per compute unit) `fixed` for its start and epilogue, and per K
+// step `step`, plus `full` times the share of the compute units that the round
+// keeps busy (the chip slows down under load, as it runs at its power limit).
+// Fitted to 98 GEMMs of the image and video blocks' projections at 100 to
+// 16,000 rows, each timed with every shape: the shape with the least estimate
+// was the fastest one or within 1% of it in all of them.  With few rows the
+// small tiles use more compute units (1,024 x 3,072 x 3,072: 57 us with 256 x
+// 256, 45 with 256 x 192, 24 with 128 x 128); with many rows a large tile
+// reads each operand less often (16,000 x 12,288 x 3,072: 857, 895 and 1,145
+// us); in between it is the rounds that decide (5,417 x 3,072 x 3,072: 124,
+// 100 and 107 us, 90 with 128 x 192).
+struct TileCost { int bm, bn; float fixed, step, full; };
+constexpr TileCost kCost[5] = {
+    {256, 256, 7.15f, 0.9445f, 0.3357f}, {256, 192, 5.97f, 0.7277f, 0.2706f}, {128, 256, 4.45f, 0.5556f, 0.1872f},
+    {128, 192, 3.34f, 0.4396f, 0.1457f}, {128, 128, 2.74f, 0.3213f, 0.1101f}};
+
+int choose_tile(int64_t M, int N, int K, int cus) {
+  const int forced = g_tile_n.load(std::memory_order_relaxed);
+  if (forced == 256) return 0;
+  if (forced == 192) return 1;
+  const float kt = (float)(K / BK);
+  int best = 0;
+  float least = 0.f;
+  for (int t = 0; t < 5; ++t) {
+    const TileCost& c = kCost[t];
+    const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+    const int64_t rounds = tiles / cus, rest = tiles % cus;
+    const float cost = (float)rounds * (c.fixed + kt * (c.step + c.full)) +
+                       (rest ? c.fixed + kt * (c.step + c.full * (float)rest / (float)cus) : 0.f);
+    if (t == 0 || cost < least) {
+      best = t;
+      least = cost;
+    }
   }
+  return best;
+}
+
+// Tile rows per raster group.  A group of G rows lets the 32 tiles resident on
+// an XCD cover G x 32 / G tiles and share their panels in its L2.  Timed with
+// 2, 3, 4, 6, 8 and 16: up to 40 tile rows 6 to 8 are fastest or within 1%
+// (9,216 x 5,120 x 5,120: 340 us with 2, 333 with 8); at 32,760 rows 4 (3.46
+// against 3.51 and 3.52 ms with 2 and 8 on the QKV shape); at 75,600 rows 3
+// (8.29 against 8.33 and 8.61 ms with 4 and 8).
+int raster(int tiles_m) { return tiles_m <= 40 ? 8 : tiles_m <= 160 ? 4 : 3; }
+
+template <int EPI, typename S>
+hipError_t launch_tiles(const LinearArgs& p, int cus, hipStream_t s) {
+  const int64_t tiles_m = (p.M + S::BM - 1) / S::BM, tiles_n = (p.N + S::BN - 1) / S::BN;
+  if (tiles_m * tiles_n > 0x7FFFFFF8ll) return hipErrorInvalidValue;
+  // one workgroup per compute unit, each running a sequence of tiles
+  int grid = (int)((tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds);
+  const int resident = cus / kXcds * kXcds;
+  if (resident >= kXcds && grid > resident) grid = resident;
+  gemm_bf16_nt<EPI, S><<<grid, kThreads, 0, s>>>(
+      (const bf16*)p.a, p.lda, (const bf16*)p.w, p.ldw, (const bf16*)p.bias, (bf16*)p.out, p.ldo,
+      (const bf16*)p.res, p.ldr, p.gate, p.gate_stride, p.req, (int)p.M, p.N, p.K, (int)tiles_m, (int)tiles_n,
+      raster((int)tiles_m), p.plane_cols, p.plane_stride - p.plane_cols);
   return hipGetLastError();
 }
 
-// Output tiles are 256 x 256, or 256 x 192 where that needs fewer rounds of
-// tiles over the compute units: with few tiles the last round leaves compute
-// units idle (4,096 rows x 3,072 columns: 192 tiles of 256 x 256 on 256 CUs,
-// but exactly 256 of 256 x 192).  A round of narrow tiles is costed at
-// 192 / 256 of a wide one, plus 8% (7 fragment reads per 12 MFMAs instead of
-// 8 per 16).
 template <int EPI>
 hipError_t launch_bf16(const LinearArgs& p, hipStream_t s) {
-  const int tiles_m = (int)((p.M + BM - 1) / BM);
   const int cus = cu_count();
-  auto rounds = [&](int bn) { return ((int64_t)tiles_m * ((p.N + bn - 1) / bn) + cus - 1) / cus; };
-  int bn = g_tile_n.load(std::memory_order_relaxed);
-  if (bn != 192 && bn != 256) bn = rounds(192) * 192 * 108 < rounds(256) * 256 * 100 ? 192 : 256;
-  if (bn == 192) return launch_bf16_tiles<EPI, 192>(p, tiles_m, (p.N + 191) / 192, s);
-  return launch_bf16_tiles<EPI, 256>(p, tiles_m, (p.N + 255) / 256, s);
+  switch (choose_tile(p.M, p.N, p.K, cus)) {
+    case 0: return launch_tiles<EPI, Tile256x256>(p, cus, s);
+    case 1: return launch_tiles<EPI, Tile256x192>(p, cus, s);
+    case 2: return launch_tiles<EPI, Tile128x256>(p, cus, s);
+    case 3: return launch_tiles<EPI, Tile128x192>(p, cus, s);
+    default: return launch_tiles<EPI, Tile128x128>(p, cus, s);
+  }
 }
 
 template <int EPI>
