@@ -40,7 +40,7 @@
 // us; 4,096 x 3,072 x 12,288 246 -> 210 us; 4,096 x 9,216 x 3,072 189 -> 161
 // us; 1,024 x 3,072 x 3,072 63 -> 27 us; 1,024 x 3,072 x 12,288 171 -> 81 us.
 //
-// fp32: a plain 64x64 LDS-tiled FMA kernel for the small exact configuration.
+// fp32 (the small exact configuration): see gemm_f32_nt.
 #include <atomic>
 #include <type_traits>
 
@@ -440,62 +440,163 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_nt(
 
 // ----------------------------------------------------------------- fp32
 
-constexpr int FT = 64;   // fp32 tile
-constexpr int FK = 16;
+// fp32 GEMM on the matrix cores (v_mfma_f32_16x16x4_f32: fp32 products and
+// sums).  The operands go from global memory straight into registers in the
+// instruction's layout: a lane's 16-byte load holds four consecutive k of one
+// row, and the four MFMAs of a 16-wide K step take element e of it, i.e. the
+// same permutation of k for both operands.
+//
+// An output element is the sum of four partial sums over the quarters of K
+// (each a multiple of 16 long), added in order, whatever the kernel:
+//  - few tiles (the small exact configuration): a workgroup per 16 x 16 tile,
+//    one wave per quarter, the partial sums meet in LDS.  64 x 384 outputs are
+//    96 workgroups of 4 waves instead of the 6 of the former 64 x 64 FMA tiles,
+//    whose one serial K loop took 47 us at K = 384 and 179 us at 1,536; now
+//    4.0 and 7.3 us;
+//  - else a workgroup per 64 x 64 tile, 32 x 32 per wave, the quarters one
+//    after the other (a quarter of the operand reads per output).
+// The small kernel reads each operand row once per 16 outputs, so its time
+// grows with M N K; the line is where both take about the same time: 16.6 and
+// 17.0 us at 256 x 2,048 x 512 (128 tiles of 64 x 64), 51 and 60 us at 800 x
+// 512 x 2,048 (104), but 20.1 and 17.1 us at 400 x 1,536 x 512 (168).  At
+// 2,048^3 the second kernel takes 236 us (73 TFLOP/s; the FMA tiles 429).
+constexpr int FK = 16;   // K step
+constexpr int64_t kF32LargeTiles = 128;   // 64 x 64 tiles from which the second kernel runs
 
+// Sums over k in [k0, k1), k0 a multiple of 4, of MB x NB blocks of 16 x 16:
+// acc[i][j][e] += W[n_i + 4 g + e] . A[m_j + r] with r = lane % 16, g = lane / 16.
+// pa, pw: the lane's rows (k = 0), clamped to the operand's last row.
+template <int MB, int NB>
+__device__ __forceinline__ void f32_span(f32x4 (&acc)[NB][MB], const float* const (&pa)[MB],
+                                         const float* const (&pw)[NB], int g, int k0, int k1) {
+  constexpr int U = MB * NB == 1 ? 8 : 2;   // K steps in flight
+  struct Step { f32x4 a[MB], w[NB]; };
+  auto load = [&](Step& s, int k) {
+#pragma unroll
+    for (int j = 0; j < MB; ++j) s.a[j] = *reinterpret_cast<const f32x4*>(pa[j] + k + 4 * g);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) s.w[i] = *reinterpret_cast<const f32x4*>(pw[i] + k + 4 * g);
+  };
+  auto mma = [&](const Step& s) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < MB; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(s.w[i][e], s.a[j][e], acc[i][j], 0, 0, 0);
+  };
+  int k = k0;
+  for (; k + FK * U <= k1; k += FK * U) {
+    Step s[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(s[u], k + FK * u);
+#pragma unroll
+    for (int u = 0; u < U; ++u) mma(s[u]);
+  }
+  if (k + FK <= k1) {   // up to U - 1 whole steps, loaded together
+    Step s[U];
+#pragma unroll
+    for (int u = 0; u + 1 < U; ++u)
+      if (k + FK * (u + 1) <= k1) load(s[u], k + FK * u);
+#pragma unroll
+    for (int u = 0; u + 1 < U; ++u)
+      if (k + FK <= k1) {
+        mma(s[u]);
+        k += FK;
+      }
+  }
+  if (k < k1) {   // the last k, one by one: a row need not be whole past k1
+    Step s{};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (k + 4 * g + e < k1) {
+#pragma unroll
+        for (int j = 0; j < MB; ++j) s.a[j][e] = pa[j][k + 4 * g + e];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) s.w[i][e] = pw[i][k + 4 * g + e];
+      }
+    mma(s);
+  }
+}
+
+// Four output columns n .. n + 3 of row m (N is a multiple of 4, so they are all inside or all outside).
 template <int EPI>
+__device__ __forceinline__ void f32_store(f32x4 z, int m, int n, const float* __restrict__ bias, float* C, int64_t ldc,
+                                          const float* R, int64_t ldr, const float* __restrict__ gate,
+                                          int64_t gate_stride, const ReqTable& req, int M, int N, int plane_cols,
+                                          int64_t plane_skip) {
+  if (m >= M || n >= N) return;
+  if (bias) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) z[e] += bias[n + e];
+  }
+  if (EPI == DIT_EPI_GELU_TANH) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) z[e] = gelu_tanh(z[e]);
+  }
+  if (EPI == DIT_EPI_RESIDUAL || EPI == DIT_EPI_GATED_RESIDUAL) {
+    const f32x4 r = *reinterpret_cast<const f32x4*>(R + (int64_t)m * ldr + n);
+    if (EPI == DIT_EPI_GATED_RESIDUAL) {
+      const f32x4 g4 = *reinterpret_cast<const f32x4*>(gate + (int64_t)find_req(req.cu, req.n_req, m) * gate_stride + n);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z[e] = r[e] + g4[e] * z[e];
+    } else {
+      z += r;
+    }
+  }
+  *reinterpret_cast<f32x4*>(C + (plane_cols > 0 ? (int64_t)(n / plane_cols) * plane_skip : 0) + (int64_t)m * ldc + n) = z;
+}
+
+// TILE 16: one 16 x 16 tile per workgroup, a quarter of K per wave; TILE 64:
+// one 64 x 64 tile, 32 x 32 per wave.
+template <int EPI, int TILE>
 __global__ __launch_bounds__(256) void gemm_f32_nt(
     const float* __restrict__ A, int64_t lda, const float* __restrict__ W, int64_t ldw,
     const float* __restrict__ bias, float* C, int64_t ldc, const float* R, int64_t ldr,
     const float* __restrict__ gate, int64_t gate_stride, ReqTable req, int M, int N, int K, int plane_cols,
     int64_t plane_skip) {
-  __shared__ float As[FK][FT + 1];
-  __shared__ float Ws[FK][FT + 1];
-  const int m0 = blockIdx.y * FT, n0 = blockIdx.x * FT;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += FK) {
-    for (int i = threadIdx.x; i < FT * FK; i += 256) {
-      int r = i / FK, kk = i % FK;
-      int am = m0 + r, wn = n0 + r, k = k0 + kk;
-      As[kk][r] = (am < M && k < K) ? A[(int64_t)am * lda + k] : 0.f;
-      Ws[kk][r] = (wn < N && k < K) ? W[(int64_t)wn * ldw + k] : 0.f;
-    }
-    __syncthreads();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, g = lane >> 4;
+  const int kq = (K + 4 * FK - 1) / (4 * FK) * FK;   // a quarter of K
+  constexpr int B = TILE == 16 ? 1 : 2;
+  const int m0 = blockIdx.y * TILE + (TILE == 16 ? 0 : 32 * (wave >> 1));
+  const int n0 = blockIdx.x * TILE + (TILE == 16 ? 0 : 32 * (wave & 1));
+  const float *pa[B], *pw[B];
 #pragma unroll
-    for (int kk = 0; kk < FK; ++kk) {
-      float a[4], w[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        a[e] = As[kk][ty * 4 + e];
-        w[e] = Ws[kk][tx * 4 + e];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
-    }
-    __syncthreads();
+  for (int b = 0; b < B; ++b) {
+    pa[b] = A + (int64_t)min(m0 + 16 * b + r, M - 1) * lda;
+    pw[b] = W + (int64_t)min(n0 + 16 * b + r, N - 1) * ldw;
   }
+  if constexpr (TILE == 16) {
+    __shared__ f32x4 part[3][64];
+    f32x4 acc[1][1] = {};
+    f32_span<1, 1>(acc, pa, pw, g, min(K, wave * kq), min(K, (wave + 1) * kq));
+    if (wave > 0) part[wave - 1][lane] = acc[0][0];
+    __syncthreads();
+    if (wave > 0) return;
+    f32x4 z = acc[0][0];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int m = m0 + ty * 4 + i;
-    if (m >= M) continue;
-    const float* g = nullptr;
-    if (EPI == DIT_EPI_GATED_RESIDUAL) g = gate + (int64_t)find_req(req.cu, req.n_req, m) * gate_stride;
+    for (int q = 0; q < 3; ++q) z += part[q][lane];
+    f32_store<EPI>(z, m0 + r, n0 + 4 * g, bias, C, ldc, R, ldr, gate, gate_stride, req, M, N, plane_cols, plane_skip);
+  } else {
+    f32x4 sum[2][2];
+    for (int q = 0; q < 4; ++q) {
+      f32x4 acc[2][2] = {};
+      f32_span<2, 2>(acc, pa, pw, g, min(K, q * kq), min(K, (q + 1) * kq));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int n = n0 + tx * 4 + j;
-      if (n >= N) continue;
-      float z = acc[i][j] + (bias ? bias[n] : 0.f);
-      if (EPI == DIT_EPI_GELU_TANH) z = gelu_tanh(z);
-      else if (EPI == DIT_EPI_RESIDUAL) z = R[(int64_t)m * ldr + n] + z;
-      else if (EPI == DIT_EPI_GATED_RESIDUAL) z = R[(int64_t)m * ldr + n] + g[n] * z;
-      C[(plane_cols > 0 ? (int64_t)(n / plane_cols) * plane_skip : 0) + (int64_t)m * ldc + n] = z;
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) sum[i][j] = q == 0 ? acc[i][j] : sum[i][j] + acc[i][j];
     }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        f32_store<EPI>(sum[i][j], m0 + 16 * j + r, n0 + 16 * i + 4 * g, bias, C, ldc, R, ldr, gate, gate_stride, req, M,
+                       N, plane_cols, plane_skip);
   }
 }
-
 
 std::atomic<int> g_tile_n{0};   // forced output tile width (0: chosen per shape)
 
@@ -581,11 +682,18 @@ hipError_t launch_bf16(const LinearArgs& p, hipStream_t s) {
 
 template <int EPI>
 hipError_t launch_f32(const LinearArgs& p, hipStream_t s) {
-  dim3 grid((p.N + FT - 1) / FT, (unsigned)((p.M + FT - 1) / FT));
-  gemm_f32_nt<EPI><<<grid, 256, 0, s>>>(
-      (const float*)p.a, p.lda, (const float*)p.w, p.ldw, (const float*)p.bias, (float*)p.out, p.ldo,
-      (const float*)p.res, p.ldr, p.gate, p.gate_stride, p.req, (int)p.M, p.N, p.K, p.plane_cols,
-      p.plane_stride - p.plane_cols);
+  // (see gemm_f32_nt)
+  const int64_t tiles = ((p.M + 63) / 64) * ((p.N + 63) / 64);
+  const bool small = tiles < kF32LargeTiles;
+  const int t = small ? 16 : 64;
+  const dim3 grid((p.N + t - 1) / t, (unsigned)((p.M + t - 1) / t));
+#define DIT_F32_ARGS                                                                                            \
+  (const float*)p.a, p.lda, (const float*)p.w, p.ldw, (const float*)p.bias, (float*)p.out, p.ldo,              \
+      (const float*)p.res, p.ldr, p.gate, p.gate_stride, p.req, (int)p.M, p.N, p.K, p.plane_cols,              \
+      p.plane_stride - p.plane_cols
+  if (small) gemm_f32_nt<EPI, 16><<<grid, 256, 0, s>>>(DIT_F32_ARGS);
+  else gemm_f32_nt<EPI, 64><<<grid, 256, 0, s>>>(DIT_F32_ARGS);
+#undef DIT_F32_ARGS
   return hipGetLastError();
 }
 
