@@ -325,7 +325,23 @@ __global__ __launch_bounds__(256) void gated_residual_kernel(
 }
 
 // ------------------------------------------------------- conditioning
+// The vectors that are inputs of a Linear of the chain are kept in an order in
+// which its lanes read them in whole lines: in every whole group of 64 VN
+// values (VN weights per 16-byte vector, one vector per lane), value
+// VN lane + 4 h + j lies at 256 h + 4 lane + j.  With bf16 weights a lane
+// needs 8 consecutive fp32 inputs, and its two 16-byte loads would each skip
+// every other 16 bytes.  (fp32 weights, and the values after the last whole
+// group: the plain order.)
+template <typename T>
+__device__ __forceinline__ int cond_at(int i, int n) {
+  constexpr int VN = Vec16<T>::n, G = 64 * VN;
+  if (VN == 4 || i - i % G + G > n) return i;
+  const int k = i % G;
+  return i - k + 256 * (k % VN / 4) + k / VN * 4 + k % 4;
+}
+
 // e[r] = [cos(t w_i), sin(t w_i)], w_i = 10000^(-i/half); computed in double.
+template <typename T>
 __global__ void timestep_embed_kernel(const float* __restrict__ t, float* __restrict__ e, int n_req,
                                       int freq_dim) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
@@ -335,119 +351,156 @@ __global__ void timestep_embed_kernel(const float* __restrict__ t, float* __rest
   const double w = exp(-log(10000.0) * (double)i / (double)half);
   double sn, cn;
   sincos((double)t[r] * w, &sn, &cn);
-  e[(int64_t)r * freq_dim + i] = (float)cn;
-  e[(int64_t)r * freq_dim + half + i] = (float)sn;
+  e[(int64_t)r * freq_dim + cond_at<T>(i, freq_dim)] = (float)cn;
+  e[(int64_t)r * freq_dim + cond_at<T>(half + i, freq_dim)] = (float)sn;
 }
 
 __device__ __forceinline__ float silu(float z) { return z / (1.0f + expf(-z)); }
 
-// y[r][o] = act(sum_i W[o][i] x[r][i] + b[o]) for up to 8 requests per pass;
-// one wave per output row, W read once per pass with 16-byte vectors.
-template <typename T, bool SILU_OUT>
+// Sums of N values (a power of two up to 64) over the wave, all at once: lane
+// l gets the sum of v[i], i the top log2(N) bits of l (so 64 / N lanes hold
+// the same).  Each halving step exchanges half of the remaining values with
+// the lane `o` away, so N sums take about N exchanges instead of 6 N; the
+// pairs added are those of wave_sum, so the bits are the same.
+template <int N, int O = 32>
+__device__ __forceinline__ float wave_sums(float (&v)[N]) {
+  if constexpr (O == 0) {
+    return v[0];
+  } else if constexpr (N == 1) {
+    float w[1] = {v[0] + __shfl_xor(v[0], O, kWave)};
+    return wave_sums<1, O / 2>(w);
+  } else {
+    float w[N / 2];
+    const bool up = threadIdx.x & O;
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+      if constexpr (O == 32) {
+        // swaps the upper half of the first with the lower half of the second
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + N / 2]), false, false);
+        w[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+      } else if constexpr (O == 16) {
+        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + N / 2]), false, false);
+        w[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+      } else {
+        w[i] = (up ? v[i + N / 2] : v[i]) + __shfl_xor(up ? v[i] : v[i + N / 2], O, kWave);
+      }
+    }
+    return wave_sums<N / 2, O / 2>(w);
+  }
+}
+
+// y[r][o] = act(sum_i W[o][i] x[r][i] + b[o]), x and y fp32.  The weights are
+// read from memory once and bound the time for few requests (the adaLN
+// projection of one request at 30,720 x 5,120, 315 MB: 52.6 us, 6.0 TB/s); a
+// wave computes ROWS outputs for up to RB requests, so the inputs it reads
+// from the caches (4 bytes per 2 of bf16 weights, request and wave) serve ROWS
+// rows, and the sums over the wave are taken all at once.  With a row per
+// wave and a tree per sum those took more time than the weights: 62.9 us for
+// one request, 147.7 for six (now 78.1).  Two vectors of every row are in
+// flight per lane.  A lane sums its vectors of a row in order, the lanes meet
+// in a tree: the same bits for every ROWS and RB.
+template <typename T, bool SILU_OUT, int ROWS, int RB>
 __global__ __launch_bounds__(256) void gemv_kernel(const T* __restrict__ W, const T* __restrict__ b,
                                                    const float* __restrict__ x, float* __restrict__ y,
                                                    int n_out, int n_in, int n_req) {
   typedef typename Vec16<T>::type V;
   constexpr int VN = Vec16<T>::n;
-  const int lane = threadIdx.x & 63;
-  const int o = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (o >= n_out) return;
-  const T* wr = W + (int64_t)o * n_in;
-  const int nv = n_in / VN;
-  for (int r0 = 0; r0 < n_req; r0 += 8) {
-    const int nr = min(8, n_req - r0);
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int c = lane; c < nv; c += 64) {
-      V wv = *reinterpret_cast<const V*>(wr + c * VN);
-#pragma unroll
-      for (int rr = 0; rr < 8; ++rr) {
-        if (rr < nr) {
-          const float* xr = x + (int64_t)(r0 + rr) * n_in + c * VN;
-#pragma unroll
-          for (int e = 0; e < VN; ++e) acc[rr] = fmaf(to_f<T>(wv[e]), xr[e], acc[rr]);
-        }
-      }
-    }
-#pragma unroll
-    for (int rr = 0; rr < 8; ++rr) {
-      if (rr < nr) {
-        float s = wave_sum(acc[rr]);
-        if (lane == 0) {
-          s += b ? to_f<T>(b[o]) : 0.f;
-          y[(int64_t)(r0 + rr) * n_out + o] = SILU_OUT ? silu(s) : s;
-        }
-      }
-    }
-  }
-}
-
-// The same product for rows of at most 64 NVL vectors: a lane loads all of
-// its NVL weight vectors of the row first, so they are in flight together
-// (the weights stream from memory once, and a wave with one load in flight
-// at a time is latency-bound), then accumulates each request over them in
-// the order of gemv_kernel (the results are the same bits).
-template <typename T, bool SILU_OUT, int NVL>
-__global__ __launch_bounds__(256) void gemv_row_kernel(const T* __restrict__ W, const T* __restrict__ b,
-                                                       const float* __restrict__ x, float* __restrict__ y,
-                                                       int n_out, int n_in, int n_req) {
-  typedef typename Vec16<T>::type V;
-  constexpr int VN = Vec16<T>::n;
   typedef float fxv __attribute__((ext_vector_type(VN)));
   const int lane = threadIdx.x & 63;
-  const int o = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (o >= n_out) return;
-  const T* wr = W + (int64_t)o * n_in;
+  const int o0 = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * ROWS;
+  if (o0 >= n_out) return;
   const int nv = n_in / VN;
-  const float bo = b ? to_f<T>(b[o]) : 0.f;
-  // FULL: every lane has all NVL vectors (no per-lane tests, so the loads
-  // are not split by branches)
-  auto run = [&](auto full) __attribute__((always_inline)) {
-    V wv[NVL];
+  const T* wr[ROWS];   // rows past the last output repeat it
 #pragma unroll
-    for (int u = 0; u < NVL; ++u) {
-      const int c = lane + 64 * u;
-      if (decltype(full)::value || c < nv) wv[u] = *reinterpret_cast<const V*>(wr + c * VN);
-    }
-    for (int r = 0; r < n_req; ++r) {
-      const float* xr = x + (int64_t)r * n_in;
-      fxv xv[NVL];   // the request's inputs under the lane's vectors, loaded together
+  for (int n = 0; n < ROWS; ++n) wr[n] = W + (int64_t)min(o0 + n, n_out - 1) * n_in;
+  for (int r0 = 0; r0 < n_req; r0 += RB) {
+    const int nr = min(RB, n_req - r0);
+    float acc[ROWS][RB] = {};
+    // FULL: every lane has its vector (no per-lane tests, so the loads are
+    // not split by branches)
+    auto run = [&](int c0, int n_vec, auto full) __attribute__((always_inline)) {
+      constexpr bool kFull = decltype(full)::value;
+      V wv[2][ROWS];
 #pragma unroll
-      for (int u = 0; u < NVL; ++u) {
-        const int c = lane + 64 * u;
-        if (decltype(full)::value || c < nv) xv[u] = *reinterpret_cast<const fxv*>(xr + c * VN);
-      }
-      float acc = 0.f;
+      for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int u = 0; u < NVL; ++u) {
-        const int c = lane + 64 * u;
-        if (decltype(full)::value || c < nv) {
+        for (int n = 0; n < ROWS; ++n) {
+          const int c = c0 + 64 * h + lane;
+          if (kFull || c < n_vec) wv[h][n] = *reinterpret_cast<const V*>(wr[n] + (int64_t)c * VN);
+        }
 #pragma unroll
-          for (int e = 0; e < VN; ++e) acc = fmaf(to_f<T>(wv[u][e]), xv[u][e], acc);
+      for (int h = 0; h < 2; ++h) {
+        const int c = c0 + 64 * h + lane;
+        fxv xv[RB];
+#pragma unroll
+        for (int rr = 0; rr < RB; ++rr) {   // requests past the last one repeat it
+          const float* xr = x + (int64_t)(r0 + min(rr, nr - 1)) * n_in;
+          if (VN == 8 && (kFull || c0 + 64 * h + 64 <= n_vec)) {   // a whole group, in the order of cond_at
+            const f32x4 lo = *reinterpret_cast<const f32x4*>(xr + (c0 + 64 * h) * VN + 4 * lane);
+            const f32x4 hi = *reinterpret_cast<const f32x4*>(xr + (c0 + 64 * h) * VN + 256 + 4 * lane);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              xv[rr][e] = lo[e];
+              xv[rr][VN - 4 + e] = hi[e];
+            }
+          } else if (kFull || c < n_vec) {
+            xv[rr] = *reinterpret_cast<const fxv*>(xr + (int64_t)c * VN);
+          }
+        }
+        if (kFull || c < n_vec) {
+#pragma unroll
+          for (int n = 0; n < ROWS; ++n)
+#pragma unroll
+            for (int rr = 0; rr < RB; ++rr)
+#pragma unroll
+              for (int e = 0; e < VN; ++e) acc[n][rr] = fmaf(to_f<T>(wv[h][n][e]), xv[rr][e], acc[n][rr]);
         }
       }
-      float sum = wave_sum(acc);
-      if (lane == 0) {
-        sum += bo;
-        y[(int64_t)r * n_out + o] = SILU_OUT ? silu(sum) : sum;
-      }
+    };
+    int c0 = 0;
+    for (; c0 + 128 <= nv; c0 += 128) run(c0, nv, std::true_type{});
+    if (c0 < nv) run(c0, nv, std::false_type{});
+    constexpr int N = ROWS * RB;
+    float v[N];
+#pragma unroll
+    for (int n = 0; n < ROWS; ++n)
+#pragma unroll
+      for (int rr = 0; rr < RB; ++rr) v[n * RB + rr] = acc[n][rr];
+    float s = wave_sums<N>(v);
+    const int n = lane / (64 / N) / RB, rr = lane / (64 / N) % RB, o = o0 + n;
+    if (lane % (64 / N) == 0 && rr < nr && o < n_out) {
+      s += b ? to_f<T>(b[o]) : 0.f;
+      // (with SiLU: an input of the next Linear)
+      y[(int64_t)(r0 + rr) * n_out + (SILU_OUT ? cond_at<T>(o, n_out) : o)] = SILU_OUT ? silu(s) : s;
     }
-  };
-  if (nv == 64 * NVL) run(std::true_type{});
-  else run(std::false_type{});
+  }
 }
 
+// Rows per wave.  4 in general; 2 for the timestep MLP of one or two requests,
+// where more waves count (12.2 against 13.3 us at 5,120 x 5,120); 8 for the
+// adaLN projection of a wide model and many requests, where the reads of x
+// do (6 requests at 30,720 x 5,120: 78.1 us against 86.2 with 4 and 127 with
+// 2; at 18,432 x 3,072 they are 33.2, 25.5 and 33.6).
 template <typename T, bool SILU_OUT>
 void launch_gemv(const T* W, const T* b, const float* x, float* y, int n_out, int n_in, int n_req, hipStream_t s) {
-  const unsigned grid = (unsigned)((n_out + 3) / 4);
-  switch ((n_in / Vec16<T>::n + 63) / 64) {
-#define DIT_GEMV_ROW(NVL) \
-  case NVL: gemv_row_kernel<T, SILU_OUT, NVL><<<grid, 256, 0, s>>>(W, b, x, y, n_out, n_in, n_req); return;
-    DIT_GEMV_ROW(1) DIT_GEMV_ROW(2) DIT_GEMV_ROW(3) DIT_GEMV_ROW(4) DIT_GEMV_ROW(5) DIT_GEMV_ROW(6)
-    DIT_GEMV_ROW(7) DIT_GEMV_ROW(8) DIT_GEMV_ROW(9) DIT_GEMV_ROW(10) DIT_GEMV_ROW(11) DIT_GEMV_ROW(12)
-    DIT_GEMV_ROW(13) DIT_GEMV_ROW(14) DIT_GEMV_ROW(15) DIT_GEMV_ROW(16)
-#undef DIT_GEMV_ROW
-    default: gemv_kernel<T, SILU_OUT><<<grid, 256, 0, s>>>(W, b, x, y, n_out, n_in, n_req);
+  auto grid = [&](int rows) { return (unsigned)((n_out + 4 * rows - 1) / (4 * rows)); };
+#define DIT_GEMV(ROWS, RB) gemv_kernel<T, SILU_OUT, ROWS, RB><<<grid(ROWS), 256, 0, s>>>(W, b, x, y, n_out, n_in, n_req)
+  if (n_req <= 2) {
+    if (n_out <= 8192) {
+      if (n_req == 1) DIT_GEMV(2, 1);
+      else DIT_GEMV(2, 2);
+    } else {
+      if (n_req == 1) DIT_GEMV(4, 1);
+      else DIT_GEMV(4, 2);
+    }
+  } else if (n_req <= 4) {
+    DIT_GEMV(4, 4);
+  } else if (n_out >= 24576) {
+    DIT_GEMV(8, 8);
+  } else {
+    DIT_GEMV(4, 8);
   }
+#undef DIT_GEMV
 }
 
 template <typename T, int NVL>
@@ -514,7 +567,7 @@ template <typename T>
 hipError_t cond_typed(const CondArgs& p, hipStream_t s) {
   if (p.w_t1) {
     const int half = p.freq_dim / 2;
-    timestep_embed_kernel<<<(p.n_req * half + 255) / 256, 256, 0, s>>>(p.t, p.e, p.n_req, p.freq_dim);
+    timestep_embed_kernel<T><<<(p.n_req * half + 255) / 256, 256, 0, s>>>(p.t, p.e, p.n_req, p.freq_dim);
     launch_gemv<T, true>((const T*)p.w_t1, (const T*)p.b_t1, p.e, p.a1, p.hidden, p.freq_dim, p.n_req, s);
     launch_gemv<T, true>((const T*)p.w_t2, (const T*)p.b_t2, p.a1, p.c, p.hidden, p.hidden, p.n_req, s);
   }
