@@ -61,3 +61,43 @@ def test_replicated():
     g = torch.randn(33, 65, device="cuda")
     whole = ([0, 0], [33, 65])
     _run(M.REPLICATED, g, [(0,) + whole, (1,) + whole], [(r,) + whole for r in (1, 2, 3, 4)])
+
+
+def test_many_boxes_mixed_units_and_order():
+    """More boxes than one launch takes, of every copy unit; then entries whose
+    destinations meet, and a chain that reads what an earlier entry wrote:
+    entries take effect in order."""
+    log("case migrate 5 -> 16 shards of 67 x 37 x 4 (1- to 16-byte units)")
+    for dtype in (torch.uint8, torch.bfloat16, torch.float32):
+        g = torch.randn(67, 37, 4, device="cuda").mul(50).to(dtype)
+        src = M.row_layout(67, list(range(5)), [37, 4])
+        dst = [(k, [a, c, 0], [b, d, 4]) for k, ((a, b), (c, d)) in enumerate(
+            ((x, x + 9 if x < 58 else 67), (y, y + 19 if y < 18 else 37)) for x in range(0, 67, 9) for y in (0, 19))]
+        n = _run(M.SHARDED, g, src, [(k, s, [min(e[0], 67), min(e[1], 37), 4]) for k, s, e in dst])
+        assert n > 16
+    B = require_gpu()
+    log("case migrate overlapping destinations and a chain")
+    f = B.MigField(M.SHARDED, (8, 16), 4, [(0, [0, 0], [8, 16]), (1, [0, 0], [8, 16]), (2, [0, 0], [8, 16])],
+                   [(3, [0, 0], [8, 16]), (4, [0, 0], [8, 16])])
+    a, b = (torch.randn(8, 16, device="cuda") for _ in range(2))
+    d0, d1 = (torch.zeros(8, 16, device="cuda") for _ in range(2))
+    entries = (B.CMigEntry * 3)()
+
+    def entry(e, src, dst, off, ext):
+        e.src_index, e.dst_index = src, dst
+        for d in range(2):
+            e.src_off[d] = e.dst_off[d] = off[d]
+            e.extent[d] = ext[d]
+        e.bytes = 4 * ext[0] * ext[1]
+
+    entry(entries[0], 0, 0, (0, 0), (8, 16))     # d0 = a
+    entry(entries[1], 1, 0, (2, 4), (3, 8))      # part of d0 = b
+    entry(entries[2], 2, 1, (0, 0), (8, 16))     # d1 = d0, which is source slice 2
+    for _ in range(20):
+        d0.zero_()
+        d1.zero_()
+        B.migration_execute(f, entries, 3, [a, b, d0], [d0, d1])
+        torch.cuda.synchronize()
+        want = a.clone()
+        want[2:5, 4:12] = b[2:5, 4:12]
+        assert torch.equal(d0, want) and torch.equal(d1, want)
