@@ -389,17 +389,23 @@ __device__ __forceinline__ float wave_sums(float (&v)[N]) {
   }
 }
 
-// y[r][o] = act(sum_i W[o][i] x[r][i] + b[o]), x and y fp32.  The weights are
-// read from memory once and bound the time for few requests (the adaLN
-// projection of one request at 30,720 x 5,120, 315 MB: 52.6 us, 6.0 TB/s); a
-// wave computes ROWS outputs for up to RB requests, so the inputs it reads
-// from the caches (4 bytes per 2 of bf16 weights, request and wave) serve ROWS
-// rows, and the sums over the wave are taken all at once.  With a row per
-// wave and a tree per sum those took more time than the weights: 62.9 us for
-// one request, 147.7 for six (now 78.1).  Two vectors of every row are in
-// flight per lane.  A lane sums its vectors of a row in order, the lanes meet
-// in a tree: the same bits for every ROWS and RB.
-template <typename T, bool SILU_OUT, int ROWS, int RB>
+// y[r][o] = act(sum_i W[o][i] x[r][i] + b[o]), x and y fp32.  The weights bound
+// the time for few requests (the adaLN projection of one request at 30,720 x
+// 5,120 bf16, 315 MB: 52.6 us, 6.0 TB/s); they are read once per RB requests
+// (from the caches after the first time, where they fit).  A wave computes
+// ROWS outputs for up to RB requests, so the inputs it reads from the caches
+// (4 bytes per 2 of bf16 weights, request and wave) serve ROWS rows, and the
+// sums over the wave are taken all at once.  With a row per wave and a tree
+// per sum those took more time than the weights: 62.9 us for one request,
+// 147.7 for six (now 78.1).  Two vectors of every row are in flight per lane.
+// A lane sums its vectors of a row in order, the lanes meet in a tree: the
+// same bits for every ROWS and RB, and as gemv_row_kernel.
+//
+// REST: code of its own for what is left over, i.e. a last group of at most 4
+// requests (instead of its last request repeated up to RB) and the whole
+// groups of 64 vectors after the last pair.  It costs registers, so it is used
+// where it pays (see launch_gemv).
+template <typename T, bool SILU_OUT, int ROWS, int RB, bool REST>
 __global__ __launch_bounds__(256) void gemv_kernel(const T* __restrict__ W, const T* __restrict__ b,
                                                    const float* __restrict__ x, float* __restrict__ y,
                                                    int n_out, int n_in, int n_req) {
@@ -413,27 +419,29 @@ __global__ __launch_bounds__(256) void gemv_kernel(const T* __restrict__ W, cons
   const T* wr[ROWS];   // rows past the last output repeat it
 #pragma unroll
   for (int n = 0; n < ROWS; ++n) wr[n] = W + (int64_t)min(o0 + n, n_out - 1) * n_in;
-  for (int r0 = 0; r0 < n_req; r0 += RB) {
-    const int nr = min(RB, n_req - r0);
-    float acc[ROWS][RB] = {};
-    // FULL: every lane has its vector (no per-lane tests, so the loads are
-    // not split by branches)
-    auto run = [&](int c0, int n_vec, auto full) __attribute__((always_inline)) {
+  // requests r0 .. r0 + nr - 1, nr at most `size`
+  auto group = [&](int r0, int nr, auto size) __attribute__((always_inline)) {
+    constexpr int G = decltype(size)::value;
+    float acc[ROWS][G] = {};
+    // the vectors from c0 on, `steps` groups of 64.  FULL: every lane has its
+    // vector (no per-lane tests, so the loads are not split by branches)
+    auto run = [&](int c0, int n_vec, auto steps, auto full) __attribute__((always_inline)) {
+      constexpr int S = decltype(steps)::value;
       constexpr bool kFull = decltype(full)::value;
-      V wv[2][ROWS];
+      V wv[S][ROWS];
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int h = 0; h < S; ++h)
 #pragma unroll
         for (int n = 0; n < ROWS; ++n) {
           const int c = c0 + 64 * h + lane;
           if (kFull || c < n_vec) wv[h][n] = *reinterpret_cast<const V*>(wr[n] + (int64_t)c * VN);
         }
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < S; ++h) {
         const int c = c0 + 64 * h + lane;
-        fxv xv[RB];
+        fxv xv[G];
 #pragma unroll
-        for (int rr = 0; rr < RB; ++rr) {   // requests past the last one repeat it
+        for (int rr = 0; rr < G; ++rr) {   // requests past the last one repeat it
           const float* xr = x + (int64_t)(r0 + min(rr, nr - 1)) * n_in;
           if (VN == 8 && (kFull || c0 + 64 * h + 64 <= n_vec)) {   // a whole group, in the order of cond_at
             const f32x4 lo = *reinterpret_cast<const f32x4*>(xr + (c0 + 64 * h) * VN + 4 * lane);
@@ -451,54 +459,173 @@ __global__ __launch_bounds__(256) void gemv_kernel(const T* __restrict__ W, cons
 #pragma unroll
           for (int n = 0; n < ROWS; ++n)
 #pragma unroll
-            for (int rr = 0; rr < RB; ++rr)
+            for (int rr = 0; rr < G; ++rr)
 #pragma unroll
               for (int e = 0; e < VN; ++e) acc[n][rr] = fmaf(to_f<T>(wv[h][n][e]), xv[rr][e], acc[n][rr]);
         }
       }
     };
+    constexpr std::integral_constant<int, 2> kTwo{};
+    constexpr std::integral_constant<int, 1> kOne{};
     int c0 = 0;
-    for (; c0 + 128 <= nv; c0 += 128) run(c0, nv, std::true_type{});
-    if (c0 < nv) run(c0, nv, std::false_type{});
-    constexpr int N = ROWS * RB;
+    for (; c0 + 128 <= nv; c0 += 128) run(c0, nv, kTwo, std::true_type{});
+    if constexpr (REST) {
+      for (; c0 + 64 <= nv; c0 += 64) run(c0, nv, kOne, std::true_type{});
+      if (c0 < nv) run(c0, nv, kOne, std::false_type{});
+    } else {
+      if (c0 < nv) run(c0, nv, kTwo, std::false_type{});
+    }
+    constexpr int N = ROWS * G;
     float v[N];
 #pragma unroll
     for (int n = 0; n < ROWS; ++n)
 #pragma unroll
-      for (int rr = 0; rr < RB; ++rr) v[n * RB + rr] = acc[n][rr];
+      for (int rr = 0; rr < G; ++rr) v[n * G + rr] = acc[n][rr];
     float s = wave_sums<N>(v);
-    const int n = lane / (64 / N) / RB, rr = lane / (64 / N) % RB, o = o0 + n;
+    const int n = lane / (64 / N) / G, rr = lane / (64 / N) % G, o = o0 + n;
     if (lane % (64 / N) == 0 && rr < nr && o < n_out) {
       s += b ? to_f<T>(b[o]) : 0.f;
       // (with SiLU: an input of the next Linear)
       y[(int64_t)(r0 + rr) * n_out + (SILU_OUT ? cond_at<T>(o, n_out) : o)] = SILU_OUT ? silu(s) : s;
     }
+  };
+  for (int r0 = 0; r0 < n_req; r0 += RB) {
+    const int nr = min(RB, n_req - r0);
+    if constexpr (REST && RB == 8) {
+      if (nr == 1) { group(r0, nr, std::integral_constant<int, 1>{}); break; }
+      if (nr == 2) { group(r0, nr, std::integral_constant<int, 2>{}); break; }
+      if (nr <= 4) { group(r0, nr, std::integral_constant<int, 4>{}); break; }
+    }
+    group(r0, nr, std::integral_constant<int, RB>{});
   }
 }
 
-// Rows per wave.  4 in general; 2 for the timestep MLP of one or two requests,
-// where more waves count (12.2 against 13.3 us at 5,120 x 5,120); 8 for the
-// adaLN projection of a wide model and many requests, where the reads of x
-// do (6 requests at 30,720 x 5,120: 78.1 us against 86.2 with 4 and 127 with
-// 2; at 18,432 x 3,072 they are 33.2, 25.5 and 33.6).
+// The same product with a row per wave, for rows of at most 64 NVL vectors: a
+// lane loads all of its NVL weight vectors first, so that they are in flight
+// together, then each request's inputs, all at once.  A Linear of few outputs
+// has too few waves for several rows per wave, and one request's Linear of a
+// few microseconds waits for its loads once instead of once per two vectors.
+template <typename T, bool SILU_OUT, int NVL>
+__global__ __launch_bounds__(256) void gemv_row_kernel(const T* __restrict__ W, const T* __restrict__ b,
+                                                       const float* __restrict__ x, float* __restrict__ y,
+                                                       int n_out, int n_in, int n_req) {
+  typedef typename Vec16<T>::type V;
+  constexpr int VN = Vec16<T>::n;
+  typedef float fxv __attribute__((ext_vector_type(VN)));
+  const int lane = threadIdx.x & 63;
+  const int o = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (o >= n_out) return;
+  const T* wr = W + (int64_t)o * n_in;
+  const int nv = n_in / VN;
+  const float bo = b ? to_f<T>(b[o]) : 0.f;
+  auto run = [&](auto full) __attribute__((always_inline)) {   // FULL: as in gemv_kernel
+    constexpr bool kFull = decltype(full)::value;
+    V wv[NVL];
+#pragma unroll
+    for (int u = 0; u < NVL; ++u) {
+      const int c = lane + 64 * u;
+      if (kFull || c < nv) wv[u] = *reinterpret_cast<const V*>(wr + c * VN);
+    }
+    for (int r = 0; r < n_req; ++r) {
+      const float* xr = x + (int64_t)r * n_in;
+      fxv xv[NVL];
+#pragma unroll
+      for (int u = 0; u < NVL; ++u) {
+        const int c = lane + 64 * u;
+        if (VN == 8 && (kFull || 64 * u + 64 <= nv)) {   // a whole group, in the order of cond_at
+          const f32x4 lo = *reinterpret_cast<const f32x4*>(xr + 64 * u * VN + 4 * lane);
+          const f32x4 hi = *reinterpret_cast<const f32x4*>(xr + 64 * u * VN + 256 + 4 * lane);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            xv[u][e] = lo[e];
+            xv[u][VN - 4 + e] = hi[e];
+          }
+        } else if (kFull || c < nv) {
+          xv[u] = *reinterpret_cast<const fxv*>(xr + c * VN);
+        }
+      }
+      float acc = 0.f;
+#pragma unroll
+      for (int u = 0; u < NVL; ++u)
+        if (kFull || lane + 64 * u < nv) {
+#pragma unroll
+          for (int e = 0; e < VN; ++e) acc = fmaf(to_f<T>(wv[u][e]), xv[u][e], acc);
+        }
+      float sum = wave_sum(acc);
+      if (lane == 0) {
+        sum += bo;
+        y[(int64_t)r * n_out + (SILU_OUT ? cond_at<T>(o, n_out) : o)] = SILU_OUT ? silu(sum) : sum;
+      }
+    }
+  };
+  if (nv == 64 * NVL) run(std::true_type{});
+  else run(std::false_type{});
+}
+
+template <typename T, bool SILU_OUT>
+bool launch_gemv_row(const T* W, const T* b, const float* x, float* y, int n_out, int n_in, int n_req, hipStream_t s) {
+  const unsigned grid = (unsigned)((n_out + 3) / 4);
+  switch ((n_in / Vec16<T>::n + 63) / 64) {
+#define DIT_GEMV_ROW(NVL) \
+  case NVL: gemv_row_kernel<T, SILU_OUT, NVL><<<grid, 256, 0, s>>>(W, b, x, y, n_out, n_in, n_req); return true;
+    DIT_GEMV_ROW(1) DIT_GEMV_ROW(2) DIT_GEMV_ROW(3) DIT_GEMV_ROW(4) DIT_GEMV_ROW(5) DIT_GEMV_ROW(6)
+    DIT_GEMV_ROW(7) DIT_GEMV_ROW(8) DIT_GEMV_ROW(9) DIT_GEMV_ROW(10) DIT_GEMV_ROW(11) DIT_GEMV_ROW(12)
+    DIT_GEMV_ROW(13) DIT_GEMV_ROW(14) DIT_GEMV_ROW(15) DIT_GEMV_ROW(16)
+#undef DIT_GEMV_ROW
+    default: return false;
+  }
+}
+
+// Which form, from the whole chain (two Linears D x D and one 6D x D) and the
+// single Linears timed against each other, in us:
+//  - one row per wave (gemv_row_kernel): one request, of fp32 weights (D = 384
+//    9.1, with 2 and 4 rows 10.4; D = 4,096 94 against 115) or of a short bf16
+//    Linear (D = 128 9.2, else 9.9); and the short fp32 ones of two requests
+//    from 2,048 inputs on (3.8 against 4.1) and of three from 384 (D = 1,024
+//    15.4 against 18.6).  At n_out = 2,048 in bf16 it no longer wins (the
+//    chain 20.3 against 19.7).
+//  - few outputs (below 2,048 for bf16, up to 2,048 for fp32): 2 rows, since 4
+//    leave less than a wave per two SIMDs; with REST (nine requests at 1,536 x
+//    1,536 5.5 against 6.4 us without, and against 9.9 with 4 rows).  From
+//    3,072 on 4 rows win (three requests 5.3 against 5.8).
+//  - one or two requests: 2 rows up to 8,192 outputs, where more waves count
+//    (12.2 against 13.3 at 5,120 x 5,120), else 4.
+//  - more: 4 rows; 8 for 5 and more requests of a wide model's adaLN projection,
+//    where the reads of x bound it (6 requests at 30,720 x 5,120: 78.1 us
+//    against 86.2 with 4; at 18,432 x 3,072 33.2 and 25.5).
+//  - fp32 with a small last group and up to 2,048 inputs: REST (nine requests
+//    at D = 1,024 22.7 against 30.9); with larger weights its registers cost
+//    more than the repeated requests (33 at D = 3,072: 345 against 274).
 template <typename T, bool SILU_OUT>
 void launch_gemv(const T* W, const T* b, const float* x, float* y, int n_out, int n_in, int n_req, hipStream_t s) {
+  constexpr bool f32 = sizeof(T) == 4;
+  const bool few = f32 ? n_out <= 2048 : n_out < 2048;
+  const bool row = n_req == 1 ? f32 || few : f32 && few && (n_req == 2 ? n_in >= 2048 : n_req == 3 && n_in >= 384);
+  if (row && launch_gemv_row<T, SILU_OUT>(W, b, x, y, n_out, n_in, n_req, s)) return;
   auto grid = [&](int rows) { return (unsigned)((n_out + 4 * rows - 1) / (4 * rows)); };
-#define DIT_GEMV(ROWS, RB) gemv_kernel<T, SILU_OUT, ROWS, RB><<<grid(ROWS), 256, 0, s>>>(W, b, x, y, n_out, n_in, n_req)
-  if (n_req <= 2) {
+#define DIT_GEMV(ROWS, RB, REST) \
+  gemv_kernel<T, SILU_OUT, ROWS, RB, REST><<<grid(ROWS), 256, 0, s>>>(W, b, x, y, n_out, n_in, n_req)
+  if (few) {
+    if (n_req == 1) DIT_GEMV(2, 1, true);
+    else if (n_req == 2) DIT_GEMV(2, 2, true);
+    else if (n_req <= 4) DIT_GEMV(2, 4, true);
+    else DIT_GEMV(2, 8, true);
+  } else if (n_req <= 2) {
     if (n_out <= 8192) {
-      if (n_req == 1) DIT_GEMV(2, 1);
-      else DIT_GEMV(2, 2);
+      if (n_req == 1) DIT_GEMV(2, 1, false);
+      else DIT_GEMV(2, 2, false);
     } else {
-      if (n_req == 1) DIT_GEMV(4, 1);
-      else DIT_GEMV(4, 2);
+      if (n_req == 1) DIT_GEMV(4, 1, false);
+      else DIT_GEMV(4, 2, false);
     }
   } else if (n_req <= 4) {
-    DIT_GEMV(4, 4);
+    DIT_GEMV(4, 4, false);
+  } else if (f32 && n_in <= 2048 && n_req > 8 && (n_req - 1) % 8 < 4) {
+    DIT_GEMV(4, 8, true);
   } else if (n_out >= 24576) {
-    DIT_GEMV(8, 8);
+    DIT_GEMV(8, 8, false);
   } else {
-    DIT_GEMV(4, 8);
+    DIT_GEMV(4, 8, false);
   }
 #undef DIT_GEMV
 }

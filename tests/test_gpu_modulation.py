@@ -49,3 +49,17 @@ def test_modulation_forms(dtype, D, F, n_req):
     assert err.item() <= 4e-6
     for r in {0, n_req // 2, n_req - 1}:
         assert torch.equal(run(t[r:r + 1].clone()), mod[r:r + 1])
+
+
+@pytest.mark.parametrize("dtype,D,F,n_req", [
+    # one row per wave: rows of 1 to 16 vectors a lane, whole and ragged, and one too long for it (a request
+    # alone, which every case compares with, takes it at these widths)
+    (torch.bfloat16, 512, 4096, 1), (torch.bfloat16, 1920, 8192, 1), (torch.bfloat16, 256, 16384, 1),
+    (torch.float32, 2048, 2048, 2), (torch.float32, 1920, 4100, 3), (torch.float32, 384, 384, 3),
+    # 2 rows per wave, and a last group of 1, 2 and 4 requests after a full one
+    (torch.bfloat16, 1920, 640, 12), (torch.bfloat16, 1536, 1536, 10), (torch.bfloat16, 2048, 2048, 9),
+    (torch.float32, 1024, 1028, 9), (torch.float32, 768, 256, 12), (torch.float32, 2048, 4, 13),
+    # 4 rows per wave with and without such a group; 8 rows
+    (torch.float32, 1920, 2044, 9), (torch.bfloat16, 4224, 128, 6)])
+def test_modulation_rows_and_last_groups(dtype, D, F, n_req):
+    test_modulation_forms(dtype, D, F, n_req)
