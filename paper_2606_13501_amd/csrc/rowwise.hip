@@ -590,9 +590,11 @@ bool launch_gemv_row(const T* W, const T* b, const float* x, float* y, int n_out
 //    3,072 on 4 rows win (three requests 5.3 against 5.8).
 //  - one or two requests: 2 rows up to 8,192 outputs, where more waves count
 //    (12.2 against 13.3 at 5,120 x 5,120), else 4.
-//  - more: 4 rows; 8 for 5 and more requests of a wide model's adaLN projection,
-//    where the reads of x bound it (6 requests at 30,720 x 5,120: 78.1 us
-//    against 86.2 with 4; at 18,432 x 3,072 33.2 and 25.5).
+//  - more: 4 rows; 8 where the reads of x bound it, for 5 and more requests
+//    from 28,672 outputs on (6 requests, 4 and 8 rows, weights from the caches:
+//    24,576 x 4,096 39.8 and 54.2, 27,648 x 4,608 47.3 and 53.4, 29,184 x 4,864
+//    71.5 and 65.5, 30,720 x 5,120 81.8 and 73.7; weights from memory: 55.0 and
+//    61.2, 69.9 and 68.2, 81.9 and 73.5, 85.6 and 77.1).
 //  - fp32 with a small last group and up to 2,048 inputs: REST (nine requests
 //    at D = 1,024 22.7 against 30.9); with larger weights its registers cost
 //    more than the repeated requests (33 at D = 3,072: 345 against 274).
@@ -622,7 +624,7 @@ void launch_gemv(const T* W, const T* b, const float* x, float* y, int n_out, in
     DIT_GEMV(4, 4, false);
   } else if (f32 && n_in <= 2048 && n_req > 8 && (n_req - 1) % 8 < 4) {
     DIT_GEMV(4, 8, true);
-  } else if (n_out >= 24576) {
+  } else if (n_out >= 28672) {
     DIT_GEMV(8, 8, false);
   } else {
     DIT_GEMV(4, 8, false);

@@ -59,7 +59,7 @@ def test_modulation_forms(dtype, D, F, n_req):
     # 2 rows per wave, and a last group of 1, 2 and 4 requests after a full one
     (torch.bfloat16, 1920, 640, 12), (torch.bfloat16, 1536, 1536, 10), (torch.bfloat16, 2048, 2048, 9),
     (torch.float32, 1024, 1028, 9), (torch.float32, 768, 256, 12), (torch.float32, 2048, 4, 13),
-    # 4 rows per wave with and without such a group; 8 rows
-    (torch.float32, 1920, 2044, 9), (torch.bfloat16, 4224, 128, 6)])
+    # 4 rows per wave with and without such a group; 8 rows from 28,672 outputs on
+    (torch.float32, 1920, 2044, 9), (torch.bfloat16, 4736, 128, 6), (torch.bfloat16, 4864, 128, 6)])
 def test_modulation_rows_and_last_groups(dtype, D, F, n_req):
     test_modulation_forms(dtype, D, F, n_req)
