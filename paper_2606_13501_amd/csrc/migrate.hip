@@ -139,7 +139,10 @@ hipError_t launch_box(const void* src, void* dst, const BoxCopy& b, hipStream_t 
 // MB, from 2 to 8 shards: 8 launches 29 us, one 8.7).
 constexpr int kBatch = 32;           // boxes per launch (the argument stays under 4 KB)
 constexpr int kUnitsPerBlock = 1024; // 4 units per thread, loaded together
-constexpr int64_t kMaxBatchUnits = (int64_t)1 << 31;   // larger boxes: box_copy_kernel (64-bit indices)
+// Units of one launch, fewer than this: 32-bit indices, and at most 2^21 + 32
+// workgroups of 256 (a launch of 2^32 work-items or more runs only in part,
+// without an error).  A larger box: box_copy_kernel (64-bit indices).
+constexpr int64_t kMaxBatchUnits = (int64_t)1 << 31;
 struct BatchBox {
   const char* src;                     // at the box's first unit
   char* dst;
@@ -265,6 +268,7 @@ extern "C" dit_status dit_migration_execute(const dit_mig_field* f, const dit_mi
   Batch batch;
   batch.n = 0;
   uint32_t blocks = 0;
+  int64_t units = 0;
   int64_t first = 0;   // first entry of the batch
   int64_t in_batch[kBatch];
   auto flush = [&]() -> dit_status {
@@ -273,6 +277,7 @@ extern "C" dit_status dit_migration_execute(const dit_mig_field* f, const dit_mi
     const hipError_t err = hipGetLastError();
     batch.n = 0;
     blocks = 0;
+    units = 0;
     if (err != hipSuccess)
       return mig_fail(DIT_ERR_HIP, "box copies from entry %lld: %s", (long long)first, hipGetErrorString(err));
     return DIT_OK;
@@ -319,7 +324,7 @@ extern "C" dit_status dit_migration_execute(const dit_mig_field* f, const dit_mi
     const int64_t total = b.rows * b.row_units;
     if (total < kMaxBatchUnits) {
       // the entries run in order: one that meets an earlier one of the batch starts the next
-      bool apart = batch.n < kBatch;
+      bool apart = batch.n < kBatch && units + total < kMaxBatchUnits;
       for (int j = 0; apart && j < batch.n; ++j) apart = independent(f, e, entries[in_batch[j]], src_bufs, dst_bufs);
       if (!apart && (st = flush()) != DIT_OK) return st;
       if (batch.n == 0) first = k;
@@ -328,6 +333,7 @@ extern "C" dit_status dit_migration_execute(const dit_mig_field* f, const dit_mi
                               (uint32_t)b.row_units, (uint32_t)b.e1, (uint32_t)b.e2, u, blocks,
                               b.s_p0, b.s_p1, b.s_p2, b.d_p0, b.d_p1, b.d_p2};
       blocks += (uint32_t)((total + kUnitsPerBlock - 1) / kUnitsPerBlock);
+      units += total;
       continue;
     }
     if ((st = flush()) != DIT_OK) return st;

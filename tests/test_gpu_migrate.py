@@ -101,3 +101,27 @@ def test_many_boxes_mixed_units_and_order():
         want = a.clone()
         want[2:5, 4:12] = b[2:5, 4:12]
         assert torch.equal(d0, want) and torch.equal(d1, want)
+
+
+def test_boxes_whose_workgroups_exceed_one_launch():
+    """Nine boxes of just under 2 GiB in 1-byte units: together more work-items
+    than a launch may have (2^32)."""
+    B = require_gpu()
+    log("case migrate 9 boxes of 2 GiB, 7-byte rows")
+    n, rows = 9, (2**31 - 1) // 7
+    free, _ = torch.cuda.mem_get_info()
+    if free < 60 << 30:
+        pytest.skip("needs 60 GiB of GPU memory")
+    shape = (n * rows, 7)
+    src = [(0, [0, 0], [n * rows, 7])]
+    dst = [(1 + k, [k * rows, 0], [(k + 1) * rows, 7]) for k in range(n)]
+    f = B.MigField(M.SHARDED, shape, 1, src, dst)
+    entries, count = B.migration_plan(f)
+    assert count == n
+    g = torch.randint(0, 255, (n * rows * 7 // 8 + 1,), device="cuda", dtype=torch.int64)
+    g = (g * 0x0101010101010101 + torch.arange(len(g), device="cuda") * 0x9E3779B97F4A7C1).view(torch.uint8)
+    out = [torch.full((rows, 7), 7, dtype=torch.uint8, device="cuda") for _ in range(n)]
+    B.migration_execute(f, entries, count, [g], out)
+    torch.cuda.synchronize()
+    for k in range(n):
+        assert torch.equal(out[k].view(-1), g[k * rows * 7:(k + 1) * rows * 7]), k
