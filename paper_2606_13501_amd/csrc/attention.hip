@@ -595,12 +595,14 @@ template <int HD>
 __global__ __launch_bounds__(256) void attn_fwd_f32(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     float* __restrict__ O, int64_t qs, int64_t ks, int64_t vs, int64_t os, int n_heads, float scale,
-    ReqTable cq, ReqTable ck) {
+    ReqTable cq, ReqTable ck, uint32_t n_items) {
   constexpr int NC = HD / 16;
   __shared__ float part_o[4][HD][17];
   __shared__ float part_m[4][16], part_l[4][16];
-  const int head = blockIdx.x % n_heads;
-  int tile = blockIdx.x / n_heads, req = 0;   // 16-row query tile, counted over the requests
+  const uint32_t item = blockIdx.y * gridDim.x + blockIdx.x;
+  if (item >= n_items) return;
+  const int head = item % n_heads;
+  int tile = item / n_heads, req = 0;   // 16-row query tile, counted over the requests
   for (;; ++req) {
     const int n = (cq.cu[req + 1] - cq.cu[req] + 15) / 16;
     if (tile < n) break;
@@ -862,16 +864,17 @@ hipError_t launch_attention(const AttnArgs& p, hipStream_t s) {
     int64_t tiles = 0;
     for (int r = 0; r < n_req; ++r) tiles += (p.cq.cu[r + 1] - p.cq.cu[r] + 15) / 16;
     if (tiles == 0) return hipSuccess;
-    if (tiles * p.n_heads > 0x7FFFFFFF) return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)(tiles * p.n_heads);
-    if (p.head_dim == 64)
-      attn_fwd_f32<64><<<grid, 256, 0, s>>>((const float*)p.q, (const float*)p.k, (const float*)p.v, (float*)p.o,
-                                            p.q_stride, p.k_stride, p.v_stride, p.o_stride, p.n_heads, p.scale, p.cq,
-                                            p.ck);
-    else
-      attn_fwd_f32<128><<<grid, 256, 0, s>>>((const float*)p.q, (const float*)p.k, (const float*)p.v, (float*)p.o,
-                                             p.q_stride, p.k_stride, p.v_stride, p.o_stride, p.n_heads, p.scale, p.cq,
-                                             p.ck);
+    const int64_t items = tiles * p.n_heads;
+    if (items > 0x7FFFFFFF) return hipErrorInvalidValue;
+    // fewer than 2^32 work-items per grid dimension (beyond, a launch runs only in part, without an error)
+    const unsigned nx = (unsigned)(items < (1 << 22) ? items : 1 << 22);
+    const dim3 grid(nx, (unsigned)((items + nx - 1) / nx));
+    auto launch = [&](auto kernel) {
+      kernel<<<grid, 256, 0, s>>>((const float*)p.q, (const float*)p.k, (const float*)p.v, (float*)p.o, p.q_stride,
+                                  p.k_stride, p.v_stride, p.o_stride, p.n_heads, p.scale, p.cq, p.ck, (uint32_t)items);
+    };
+    if (p.head_dim == 64) launch(attn_fwd_f32<64>);
+    else launch(attn_fwd_f32<128>);
     return hipGetLastError();
   }
   AttnWork w;

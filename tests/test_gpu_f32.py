@@ -100,3 +100,20 @@ def test_attention_f32_minus_infinity():
     torch.cuda.synchronize()
     p = torch.softmax(q.double() @ k[~dead].double().T / 8.0, -1)
     assert (out.double() - p @ v[~dead].double()).abs().max().item() <= 5e-6
+
+
+def test_attention_f32_work_items_beyond_one_grid_dimension():
+    """2^24 + 64 workgroups of 256: 2^32 work-items and more do not fit one grid
+    dimension.  With one key every output row is its value row, exactly."""
+    B = require_gpu()
+    H, d, n = 64, 64, (1 << 22) + 16
+    log(f"case attention f32 {n} queries x {H} heads")
+    if torch.cuda.mem_get_info()[0] < 160 << 30:
+        pytest.skip("needs 160 GiB of GPU memory")
+    q = torch.zeros(n, H * d, device="cuda")
+    k, v = _rand(1, H * d, seed=11), _rand(1, H * d, seed=12)
+    out = torch.full((n, H * d), 7.0, device="cuda")
+    B.attention_varlen(q, k, v, out, [0, n], [0, 1], H, d)
+    torch.cuda.synchronize()
+    for part in out.split(1 << 18):
+        assert torch.equal(part, v.expand(len(part), -1))
