@@ -35,6 +35,7 @@
 // exact online softmax.
 #include <float.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <type_traits>
@@ -591,22 +592,40 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(bf16* __restrict__ O, i
 // thread per (query, head) with a serial loop over the keys, as before, took
 // 111 us at 64 tokens x 6 heads of 64 and 2,269 us at 400 x 4 heads of 128;
 // now 7.2 and 21.3 us (4,096 x 12 heads of 64: 11.7 -> 0.80 ms).
-template <int HD>
-__global__ __launch_bounds__(256) void attn_fwd_f32(
+//
+// WAVES 1, for a launch of at most 16 keys per request: the only key tile of a
+// request is wave 0's, so its output needs no meeting (the same bits).  Three
+// idle waves and their LDS made few keys slower than one thread per (query,
+// head): 64 requests of one query and key x 6 heads of 64 5.7 us then, 8.4 with
+// four waves, 4.6 now; 64 of three x 40 heads of 128 24.1, 30.7, 11.6;
+// 4,096 queries x 6 heads, one key 7.5, 8.1, 6.0.
+template <int HD, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void attn_fwd_f32(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     float* __restrict__ O, int64_t qs, int64_t ks, int64_t vs, int64_t os, int n_heads, float scale,
     ReqTable cq, ReqTable ck, uint32_t n_items) {
   constexpr int NC = HD / 16;
-  __shared__ float part_o[4][HD][17];
-  __shared__ float part_m[4][16], part_l[4][16];
   const uint32_t item = blockIdx.y * gridDim.x + blockIdx.x;
   if (item >= n_items) return;
   const int head = item % n_heads;
   int tile = item / n_heads, req = 0;   // 16-row query tile, counted over the requests
-  for (;; ++req) {
-    const int n = (cq.cu[req + 1] - cq.cu[req] + 15) / 16;
-    if (tile < n) break;
-    tile -= n;
+  if (cq.n_req > 8) {   // lane i counts request i (the serial search took 3 us for 64 requests)
+    const int i = threadIdx.x & 63;
+    const int n = i < cq.n_req ? (cq.cu[i + 1] - cq.cu[i] + 15) / 16 : 0;
+    int sum = n;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int below = __shfl_up(sum, o, kWave);
+      if (i >= o) sum += below;
+    }
+    req = __builtin_ctzll(__ballot(sum > tile));   // a lane has the item's tile, as item < n_items
+    tile = __builtin_amdgcn_readfirstlane(tile - __shfl(sum - n, req, kWave));
+  } else {
+    for (;; ++req) {
+      const int n = (cq.cu[req + 1] - cq.cu[req] + 15) / 16;
+      if (tile < n) break;
+      tile -= n;
+    }
   }
   const int q0 = cq.cu[req] + 16 * tile, q_end = cq.cu[req + 1];
   const int kb = ck.cu[req], n_k = ck.cu[req + 1] - kb;
@@ -620,7 +639,7 @@ __global__ __launch_bounds__(256) void attn_fwd_f32(
     acc[c] = f32x4{};
   }
   float m = -INFINITY, l = 0.f;
-  for (int t = wave * 16; t < n_k; t += 64) {
+  for (int t = wave * 16; t < n_k; t += 16 * WAVES) {
     const float* kp = K + (int64_t)(kb + min(t + r, n_k - 1)) * ks + head * HD + 4 * g;
     f32x4 kf[NC];
 #pragma unroll
@@ -663,6 +682,16 @@ __global__ __launch_bounds__(256) void attn_fwd_f32(
   }
   l += __shfl_xor(l, 16, kWave);
   l += __shfl_xor(l, 32, kWave);
+  if constexpr (WAVES == 1) {
+    if (q0 + r >= q_end) return;
+    const float inv = n_k > 0 ? 1.0f / l : 0.f;
+    float* op = O + (int64_t)(q0 + r) * os + head * HD + 4 * g;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) *reinterpret_cast<f32x4*>(op + 16 * c) = (acc[c] + 0.f) * inv;   // (-0: 0, as the sum below)
+    return;
+  }
+  __shared__ float part_o[WAVES][HD][17];
+  __shared__ float part_m[WAVES][16], part_l[WAVES][16];
   if (g == 0) {
     part_m[wave][r] = m;
     part_l[wave][r] = l;
@@ -677,10 +706,10 @@ __global__ __launch_bounds__(256) void attn_fwd_f32(
   if (q0 + row >= q_end) return;
   float top = -INFINITY;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) top = fmaxf(top, part_m[w][row]);
-  float weight[4], sum = 0.f;
+  for (int w = 0; w < WAVES; ++w) top = fmaxf(top, part_m[w][row]);
+  float weight[WAVES], sum = 0.f;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
+  for (int w = 0; w < WAVES; ++w) {
     weight[w] = 16 * w < n_k ? expf(part_m[w][row] - top) : 0.f;   // waves without keys count nothing
     sum = fmaf(weight[w], part_l[w][row], sum);
   }
@@ -690,7 +719,7 @@ __global__ __launch_bounds__(256) void attn_fwd_f32(
   for (int c = 0; c < NC; ++c) {
     float o = 0.f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w)
+    for (int w = 0; w < WAVES; ++w)
       if (16 * w < n_k) o = fmaf(weight[w], part_o[w][d + 16 * c][row], o);
     op[d + 16 * c] = o * inv;
   }
@@ -869,12 +898,16 @@ hipError_t launch_attention(const AttnArgs& p, hipStream_t s) {
     // fewer than 2^32 work-items per grid dimension (beyond, a launch runs only in part, without an error)
     const unsigned nx = (unsigned)(items < (1 << 22) ? items : 1 << 22);
     const dim3 grid(nx, (unsigned)((items + nx - 1) / nx));
+    int most = 0;   // keys of a request
+    for (int r = 0; r < n_req; ++r) most = std::max(most, p.ck.cu[r + 1] - p.ck.cu[r]);
+    const bool one = most <= 16;   // (see attn_fwd_f32)
     auto launch = [&](auto kernel) {
-      kernel<<<grid, 256, 0, s>>>((const float*)p.q, (const float*)p.k, (const float*)p.v, (float*)p.o, p.q_stride,
-                                  p.k_stride, p.v_stride, p.o_stride, p.n_heads, p.scale, p.cq, p.ck, (uint32_t)items);
+      kernel<<<grid, one ? 64 : 256, 0, s>>>((const float*)p.q, (const float*)p.k, (const float*)p.v, (float*)p.o,
+                                             p.q_stride, p.k_stride, p.v_stride, p.o_stride, p.n_heads, p.scale, p.cq,
+                                             p.ck, (uint32_t)items);
     };
-    if (p.head_dim == 64) launch(attn_fwd_f32<64>);
-    else launch(attn_fwd_f32<128>);
+    if (p.head_dim == 64) one ? launch(attn_fwd_f32<64, 1>) : launch(attn_fwd_f32<64, 4>);
+    else one ? launch(attn_fwd_f32<128, 1>) : launch(attn_fwd_f32<128, 4>);
     return hipGetLastError();
   }
   AttnWork w;

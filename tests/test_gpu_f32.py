@@ -102,6 +102,35 @@ def test_attention_f32_minus_infinity():
     assert (out.double() - p @ v[~dead].double()).abs().max().item() <= 5e-6
 
 
+@pytest.mark.parametrize("times", [1, 9])   # 7 and 63 requests (the search for a tile's request)
+@pytest.mark.parametrize("H,d", [(5, 64), (3, 128)])
+def test_attention_f32_few_keys(H, d, times):
+    """Up to 16 keys per request (one wave per tile): against float64, and the
+    bits of the same requests beside one of 17 keys (four waves)."""
+    B = require_gpu()
+    log(f"case attention f32 few keys H={H} d={d}")
+    lq, lk = [1, 17, 3, 0, 16, 40, 2] * times, [1, 16, 0, 3, 15, 2, 9] * times
+    W = H * d
+    q, k, v = _rand(sum(lq) + 5, W, seed=13), _rand(sum(lk) + 17, W, seed=14), _rand(sum(lk) + 17, W, seed=15)
+
+    def run(lq, lk):
+        out = torch.full((sum(lq), W), 7.0, device="cuda")
+        B.attention_varlen(q[:sum(lq)], k[:sum(lk)], v[:sum(lk)], out, [0] + list(np.cumsum(lq)),
+                           [0] + list(np.cumsum(lk)), H, d)
+        torch.cuda.synchronize()
+        return out
+
+    out = run(lq, lk)
+    assert torch.equal(out.view(torch.int32), run(lq + [5], lk + [17])[:sum(lq)].view(torch.int32))
+    a = e = 0
+    for nq, nk in zip(lq, lk):
+        for h in range(H):
+            c = slice(h * d, (h + 1) * d)
+            p = torch.softmax(q[a:a + nq, c].double() @ k[e:e + nk, c].double().T / d ** 0.5, -1)
+            assert (out[a:a + nq, c].double() - p @ v[e:e + nk, c].double()).abs().le(5e-6).all()
+        a, e = a + nq, e + nk
+
+
 def test_attention_f32_work_items_beyond_one_grid_dimension():
     """2^24 + 64 workgroups of 256: 2^32 work-items and more do not fit one grid
     dimension.  With one key every output row is its value row, exactly."""
