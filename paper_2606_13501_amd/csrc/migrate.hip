@@ -136,10 +136,25 @@ hipError_t launch_box(const void* src, void* dst, const BoxCopy& b, hipStream_t 
 
 // Several boxes in one launch: a plan is a handful of boxes of a megabyte or
 // so each, and a launch per box costs more than its copy (the 720p latent, 19.4
-// MB, from 2 to 8 shards: 8 launches 29 us, one 8.7).
+// MB, from 2 to 8 shards: 8 launches 22.7 us, one 7.4).
+//
+// A thread copies UPT units, loaded together.
+//  - 1 for long rows (or rows that follow each other) of 16-byte units, where more and smaller workgroups stream
+//    better (75,600 x 5,120 bf16, 8 row bands to 7: 245 us, with 4 units 277, a
+//    launch per box 280; to 3 from 2: 245, 275, 263; the 720p latent as one box
+//    6.8, 8.2, 7.6), and for at most kFewUnits, where the time is one
+//    workgroup's latency (1,000 x 64 bf16 as one box: 2.2, 3.3, 2.4 us);
+//  - 4 for many units in short rows or of fewer bytes, which are bound by their
+//    index arithmetic (32,760 x 5,120 bf16, 2 row bands to 3 column bands: 332
+//    us, with one unit 437, a launch per box 489).  The line is where one unit
+//    stops winning: 1.0 M units of 33-byte rows 4.2 to 5.0 us against 4.9 to
+//    5.4, 2.0 M 6.2 to 8.0 against 7.0 to 8.3, 3.3 M 9.0 to 11.4 against 9.9 to
+//    11.4; rows of 16 to 42 bytes 7.3 against 14.5 at 0.8 M, 13.8 against 12.9
+//    at 2.6 M.
 constexpr int kBatch = 32;           // boxes per launch (the argument stays under 4 KB)
-constexpr int kUnitsPerBlock = 1024; // 4 units per thread, loaded together
-// Units of one launch, fewer than this: 32-bit indices, and at most 2^21 + 32
+constexpr int64_t kFewUnits = (int64_t)1 << 20;
+constexpr int64_t kLongRow = 64;     // units: a wave's access is one piece of memory
+// Units of one launch, fewer than this: 32-bit indices, and at most 2^23 + 32
 // workgroups of 256 (a launch of 2^32 work-items or more runs only in part,
 // without an error).  A larger box: box_copy_kernel (64-bit indices).
 constexpr int64_t kMaxBatchUnits = (int64_t)1 << 31;
@@ -148,22 +163,22 @@ struct BatchBox {
   char* dst;
   uint32_t total, row_units, e1, e2;   // total < 2^31
   int unit;                            // bytes
-  uint32_t block0;                     // first workgroup
   int64_t s_p0, s_p1, s_p2, d_p0, d_p1, d_p2;   // pitches in units
 };
 struct Batch {
   int n;
+  uint32_t block0[kBatch];             // first workgroup of each box
   BatchBox box[kBatch];
 };
 
-template <typename U>
+template <typename U, int UPT>
 __device__ __forceinline__ void copy_units(const BatchBox b, uint32_t first) {
   const U* const src = reinterpret_cast<const U*>(b.src);
   U* const dst = reinterpret_cast<U*>(b.dst);
-  U v[4];
-  int64_t to[4];
+  U v[UPT];
+  int64_t to[UPT];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
+  for (int u = 0; u < UPT; ++u) {
     const uint32_t idx = first + 256 * u;
     if (idx < b.total) {
       const uint32_t r = idx / b.row_units, c = idx - r * b.row_units;
@@ -173,23 +188,50 @@ __device__ __forceinline__ void copy_units(const BatchBox b, uint32_t first) {
     }
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int u = 0; u < UPT; ++u)
     if (first + 256 * u < b.total) dst[to[u]] = v[u];
 }
 
+template <int UPT>
 __global__ __launch_bounds__(256) void batch_copy_kernel(Batch batch) {
-  int k = 0;
-  while (k + 1 < batch.n && blockIdx.x >= batch.box[k + 1].block0) ++k;
-  k = __builtin_amdgcn_readfirstlane(k);   // uniform: the box is read from the arguments into scalars
-  const BatchBox b = batch.box[k];
-  const uint32_t first = (blockIdx.x - b.block0) * kUnitsPerBlock + threadIdx.x;
-  switch (b.unit) {   // uniform
-    case 16: copy_units<dit::u32x4>(b, first); break;
-    case 8: copy_units<dit::u32x2>(b, first); break;
-    case 4: copy_units<uint32_t>(b, first); break;
-    case 2: copy_units<uint16_t>(b, first); break;
-    default: copy_units<uint8_t>(b, first); break;
+  int k = 0;   // the workgroup's box; uniform, so that it is read from the arguments into scalars
+  if (batch.n > 8) {   // all at once (14 boxes of 3 MB: 13.0 us, one by one 14.1; up to 8 one by one is faster)
+    const int i = threadIdx.x & 63;
+    k = __builtin_popcountll(__ballot(i < batch.n && blockIdx.x >= batch.block0[i & (kBatch - 1)])) - 1;
+  } else {
+    while (k + 1 < batch.n && blockIdx.x >= batch.block0[k + 1]) ++k;
   }
+  k = __builtin_amdgcn_readfirstlane(k);
+  const BatchBox b = batch.box[k];
+  const uint32_t first = (blockIdx.x - batch.block0[k]) * (256 * UPT) + threadIdx.x;
+  switch (b.unit) {   // uniform
+    case 16: copy_units<dit::u32x4, UPT>(b, first); break;
+    case 8: copy_units<dit::u32x2, UPT>(b, first); break;
+    case 4: copy_units<uint32_t, UPT>(b, first); break;
+    case 2: copy_units<uint16_t, UPT>(b, first); break;
+    default: copy_units<uint8_t, UPT>(b, first); break;
+  }
+}
+
+hipError_t launch_batch(Batch& batch, hipStream_t s) {
+  int64_t units = 0;
+  bool one = true;
+  for (int k = 0; k < batch.n; ++k) {
+    units += batch.box[k].total;
+    const BatchBox& b = batch.box[k];
+    const bool dense = b.s_p2 == b.row_units && b.d_p2 == b.row_units;   // rows follow each other on both sides
+    one = one && b.unit == 16 && (int64_t)b.row_units * (dense ? b.e2 : 1) >= kLongRow;
+  }
+  one = one || units <= kFewUnits;
+  const uint32_t per_block = one ? 256 : 1024;
+  uint32_t blocks = 0;
+  for (int k = 0; k < batch.n; ++k) {
+    batch.block0[k] = blocks;
+    blocks += (batch.box[k].total + per_block - 1) / per_block;
+  }
+  if (one) batch_copy_kernel<1><<<blocks, 256, 0, s>>>(batch);
+  else batch_copy_kernel<4><<<blocks, 256, 0, s>>>(batch);
+  return hipGetLastError();
 }
 
 int64_t slice_bytes(const dit_mig_field* f, const dit_mig_slice& s) {
@@ -267,16 +309,13 @@ extern "C" dit_status dit_migration_execute(const dit_mig_field* f, const dit_mi
   }
   Batch batch;
   batch.n = 0;
-  uint32_t blocks = 0;
   int64_t units = 0;
   int64_t first = 0;   // first entry of the batch
   int64_t in_batch[kBatch];
   auto flush = [&]() -> dit_status {
     if (batch.n == 0) return DIT_OK;
-    batch_copy_kernel<<<blocks, 256, 0, stream>>>(batch);
-    const hipError_t err = hipGetLastError();
+    const hipError_t err = launch_batch(batch, stream);
     batch.n = 0;
-    blocks = 0;
     units = 0;
     if (err != hipSuccess)
       return mig_fail(DIT_ERR_HIP, "box copies from entry %lld: %s", (long long)first, hipGetErrorString(err));
@@ -330,9 +369,8 @@ extern "C" dit_status dit_migration_execute(const dit_mig_field* f, const dit_mi
       if (batch.n == 0) first = k;
       in_batch[batch.n] = k;
       batch.box[batch.n++] = {(const char*)sp + b.s_base * u, (char*)dp + b.d_base * u, (uint32_t)total,
-                              (uint32_t)b.row_units, (uint32_t)b.e1, (uint32_t)b.e2, u, blocks,
+                              (uint32_t)b.row_units, (uint32_t)b.e1, (uint32_t)b.e2, u,
                               b.s_p0, b.s_p1, b.s_p2, b.d_p0, b.d_p1, b.d_p2};
-      blocks += (uint32_t)((total + kUnitsPerBlock - 1) / kUnitsPerBlock);
       units += total;
       continue;
     }

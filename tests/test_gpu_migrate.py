@@ -64,10 +64,10 @@ def test_replicated():
 
 
 def test_many_boxes_mixed_units_and_order():
-    """More boxes than one launch takes, of every copy unit; then entries whose
+    """Twenty boxes in one launch (4-, 8- and 16-byte units); then entries whose
     destinations meet, and a chain that reads what an earlier entry wrote:
     entries take effect in order."""
-    log("case migrate 5 -> 16 shards of 67 x 37 x 4 (1- to 16-byte units)")
+    log("case migrate 5 -> 16 shards of 67 x 37 x 4 (4- to 16-byte units)")
     for dtype in (torch.uint8, torch.bfloat16, torch.float32):
         g = torch.randn(67, 37, 4, device="cuda").mul(50).to(dtype)
         src = M.row_layout(67, list(range(5)), [37, 4])
@@ -125,3 +125,33 @@ def test_boxes_whose_workgroups_exceed_one_launch():
     torch.cuda.synchronize()
     for k in range(n):
         assert torch.equal(out[k].view(-1), g[k * rows * 7:(k + 1) * rows * 7]), k
+
+
+def _bands(n, shape, axis):
+    cut = [shape[axis] * k // n for k in range(n + 1)]
+    return [(k, [a if d == axis else 0 for d in range(len(shape))], [b if d == axis else shape[d] for d in range(len(shape))])
+            for k, (a, b) in enumerate(zip(cut, cut[1:]))]
+
+
+@pytest.mark.parametrize("dtype,shape,src,dst,entries", [
+    # 9 x 8 boxes: three launches; 1-, 2-, 4- and 16-byte units in one launch (rows of 52 to 112 bytes)
+    (torch.uint8, (90, 640), (9, 0), [0, 112, 164, 222, 225, 230, 400, 528, 640], 72),
+    (torch.bfloat16, (45, 9, 333), (7, 0), (11, 2), 77),
+    # few units and many (about 2^20), in 8 boxes (searched one by one) and 9 or more (at once)
+    (torch.float32, (1 << 15, 31), (1, 0), (8, 0), 8), (torch.float32, (1 << 15, 33), (1, 0), (8, 0), 8),
+    (torch.float32, (1 << 15, 33), (1, 0), (9, 0), 9), (torch.uint8, (1100, 1001), (2, 0), (5, 1), 10),
+    # 16-byte units: rows of 63, 64 and 65 units, following each other or not
+    (torch.float32, (20000, 252), (1, 0), (1, 0), 1), (torch.float32, (20000, 256), (2, 0), (3, 0), 4),
+    (torch.float32, (20000, 260), (8, 0), (7, 0), 14),
+    (torch.float32, (20000, 504), (2, 0), (2, 1), 4), (torch.float32, (20000, 512), (1, 1), (2, 1), 2),
+])
+def test_launch_forms(dtype, shape, src, dst, entries):
+    """Units per thread and the search for a workgroup's box, at their lines;
+    plans of more boxes than two launches take."""
+    log(f"case migrate {dtype} {shape} {src} -> {dst}")
+    g = torch.randint(0, 255, shape, device="cuda", dtype=torch.int32).to(dtype)
+    if isinstance(dst, list):
+        to = [(k, [0, a], [shape[0], b]) for k, (a, b) in enumerate(zip(dst, dst[1:]))]
+    else:
+        to = _bands(dst[0], shape, dst[1])
+    assert _run(M.SHARDED, g, _bands(src[0], shape, src[1]), to) == entries
