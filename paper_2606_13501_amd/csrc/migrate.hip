@@ -139,11 +139,12 @@ hipError_t launch_box(const void* src, void* dst, const BoxCopy& b, hipStream_t 
 // MB, from 2 to 8 shards: 8 launches 22.7 us, one 7.4).
 //
 // A thread copies UPT units, loaded together.
-//  - 1 for long rows (or rows that follow each other) of 16-byte units, where more and smaller workgroups stream
-//    better (75,600 x 5,120 bf16, 8 row bands to 7: 245 us, with 4 units 277, a
-//    launch per box 280; to 3 from 2: 245, 275, 263; the 720p latent as one box
-//    6.8, 8.2, 7.6), and for at most kFewUnits, where the time is one
-//    workgroup's latency (1,000 x 64 bf16 as one box: 2.2, 3.3, 2.4 us);
+//  - 1 for long rows (or rows that follow each other) of 16-byte units, where
+//    more and smaller workgroups stream better (75,600 x 5,120 bf16, 8 row
+//    bands to 7: 245 us, with 4 units 277, a launch per box 280; 2 to 3: 245,
+//    275, 263; the 720p latent as one box 6.8, 8.2, 7.6), and for at most
+//    kFewUnits, where the time is one workgroup's latency (1,000 x 64 bf16 as
+//    one box: 2.3, 3.3, 2.4 us);
 //  - 4 for many units in short rows or of fewer bytes, which are bound by their
 //    index arithmetic (32,760 x 5,120 bf16, 2 row bands to 3 column bands: 332
 //    us, with one unit 437, a launch per box 489).  The line is where one unit
