@@ -240,6 +240,11 @@ dit_status dit_linear(const void *a, int64_t lda, const void *w, int64_t ldw,
  * calls). */
 dit_status dit_debug_gemm_tile_n(int tile_n);
 
+/* The output tile (*tile_m x *tile_n) that a bf16 GEMM of M x N outputs over K
+ * takes on a GPU of `compute_units` compute units, under the current debug
+ * setting.  Host arithmetic only: no device is used. */
+dit_status dit_debug_gemm_plan(int64_t M, int N, int K, int compute_units, int *tile_m, int *tile_n);
+
 /* The bf16 self-attention (key ranges over 1024) runs its work items in
  * rounds of one workgroup per compute unit.  When the last round would be at
  * most half full (one request), its items are split into 2 or 4 key pieces

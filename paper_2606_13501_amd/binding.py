@@ -155,6 +155,7 @@ def lib() -> ctypes.CDLL:
         "dit_migration_execute": (i32, [ctypes.POINTER(CMigField), ctypes.POINTER(CMigEntry), i64,
                                         ctypes.POINTER(vp), ctypes.POINTER(vp), vp]),
         "dit_debug_gemm_tile_n": (i32, [i32]),
+        "dit_debug_gemm_plan": (i32, [i64, i32, i32, i32, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
         "dit_debug_attention_split": (i32, [i32]),
         "dit_debug_attention_shape": (i32, [i32]),
         "dit_debug_attention_plan": (i32, [ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32), i32, i32, i32,
@@ -179,7 +180,7 @@ def exported_symbols() -> Sequence[str]:
                         "dit_adaln_modulate", "dit_layer_norm_affine", "dit_linear", "dit_qk_norm_rope",
                         "dit_gated_residual", "dit_text_kv_elems", "dit_text_kv", "dit_denoise_workspace_size",
                         "dit_denoise_step", "dit_patchify", "dit_unpatchify_euler", "dit_simulate",
-                        "dit_migration_plan", "dit_migration_execute", "dit_debug_gemm_tile_n",
+                        "dit_migration_plan", "dit_migration_execute", "dit_debug_gemm_tile_n", "dit_debug_gemm_plan",
                         "dit_debug_attention_split", "dit_debug_attention_shape", "dit_debug_attention_plan",
                         "dit_status_string",
                         "dit_last_error", "dit_abi_version")]
@@ -292,6 +293,14 @@ def block_post_attention(cfg, weights, vl, x, o, txt, mod, y, ws, stream=None, t
 def debug_gemm_tile_n(tile_n: int):
     """Force the bf16 GEMM's output tile width (192 or 256); 0 restores the choice per shape."""
     _check(lib().dit_debug_gemm_tile_n(int(tile_n)), "dit_debug_gemm_tile_n")
+
+
+def debug_gemm_plan(M: int, N: int, K: int, compute_units: int):
+    """(rows, columns) of the output tiles that a bf16 GEMM of this size takes (host only)."""
+    tm, tn = ctypes.c_int(), ctypes.c_int()
+    _check(lib().dit_debug_gemm_plan(int(M), int(N), int(K), int(compute_units), ctypes.byref(tm), ctypes.byref(tn)),
+           "dit_debug_gemm_plan")
+    return tm.value, tn.value
 
 
 def debug_attention_split(mode: int):

@@ -780,6 +780,18 @@ dit_status dit_debug_gemm_tile_n(int tile_n) {
   return DIT_OK;
 }
 
+dit_status dit_debug_gemm_plan(int64_t M, int N, int K, int compute_units, int* tile_m, int* tile_n) {
+  g_last_error.clear();
+  if (M < 1 || M > 0x7FFFFFFF || N < 1 || K < 1)
+    return fail(DIT_ERR_INVALID_ARG, "bad GEMM size M=%lld N=%d K=%d", (long long)M, N, K);
+  if (K % 64 || N % 8) return fail(DIT_ERR_UNSUPPORTED, "bf16 GEMM needs K %% 64 == 0 and N %% 8 == 0 (K=%d N=%d)", K, N);
+  if (compute_units < 1 || compute_units > 65536)
+    return fail(DIT_ERR_INVALID_ARG, "compute_units = %d outside 1..65536", compute_units);
+  if (!tile_m || !tile_n) return fail(DIT_ERR_INVALID_ARG, "an output pointer is NULL");
+  gemm_plan(M, N, K, compute_units, tile_m, tile_n);
+  return DIT_OK;
+}
+
 dit_status dit_debug_attention_split(int mode) {
   g_last_error.clear();
   if (mode != 0 && mode != 1 && mode != 2 && mode != 4)

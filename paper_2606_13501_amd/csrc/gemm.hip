@@ -714,6 +714,12 @@ int cu_count() {
 
 void set_gemm_tile_n(int bn) { g_tile_n.store(bn, std::memory_order_relaxed); }
 
+void gemm_plan(int64_t M, int N, int K, int cus, int* tile_m, int* tile_n) {
+  const TileCost& c = kCost[choose_tile(M, N, K, cus)];
+  *tile_m = c.bm;
+  *tile_n = c.bn;
+}
+
 hipError_t launch_linear(const LinearArgs& p, hipStream_t s) {
   if (p.M == 0) return hipSuccess;
   if (p.dtype == DIT_BF16) {

@@ -32,6 +32,8 @@ hipError_t launch_linear(const LinearArgs& p, hipStream_t s);
 int cu_count();
 // Forces the bf16 GEMM's output tile width (192 or 256; 0: chosen per shape).
 void set_gemm_tile_n(int bn);
+// The output tile of a bf16 GEMM on `cus` compute units.
+void gemm_plan(int64_t M, int N, int K, int cus, int* tile_m, int* tile_n);
 
 struct AttnArgs {
   const void *q, *k, *v;

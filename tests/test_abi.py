@@ -164,6 +164,30 @@ def _cum(lens):
     return out
 
 
+def test_gemm_plan():
+    """The bf16 GEMM's tile on 256 compute units (host arithmetic): small tiles
+    where few rows leave compute units idle, 256 x 256 with many rows, and the
+    forced widths."""
+    L = _lib()
+    for (M, N, K), want in {(1, 8, 64): (128, 128), (1024, 3072, 3072): (128, 128), (2641, 9216, 3072): (128, 256),
+                            (5417, 3072, 3072): (128, 192), (4096, 3072, 3072): (256, 192),
+                            (75600, 15360, 5120): (256, 256)}.items():
+        assert B.debug_gemm_plan(M, N, K, 256) == want, (M, N, K)
+    try:
+        for width in (192, 256):
+            B.debug_gemm_tile_n(width)
+            assert B.debug_gemm_plan(1024, 3072, 3072, 256) == (256, width)
+    finally:
+        B.debug_gemm_tile_n(0)
+    tm, tn = ctypes.c_int(), ctypes.c_int()
+    out = (ctypes.byref(tm), ctypes.byref(tn))
+    for bad in ((0, 8, 64, 256), (1, 0, 64, 256), (1, 8, 0, 256), (1, 8, 64, 0)):
+        assert L.dit_debug_gemm_plan(*bad, *out) == B.DIT_ERR_INVALID_ARG
+    assert L.dit_debug_gemm_plan(1, 12, 64, 256, *out) == B.DIT_ERR_UNSUPPORTED
+    assert L.dit_debug_gemm_plan(1, 8, 96, 256, *out) == B.DIT_ERR_UNSUPPORTED
+    assert L.dit_debug_gemm_plan(1, 8, 64, 256, None, out[1]) == B.DIT_ERR_INVALID_ARG
+
+
 def test_attention_plan_per_launch():
     """The bf16 attention's shape and split per launch on 256 compute units
     (host arithmetic).  Self-attention of one request: the 4-wave shape where
