@@ -363,8 +363,8 @@ dit_status text_kv_impl(const dit_block_config* c, const dit_block_weights* w, i
 // event, for the text key/value projection: it depends on the text and the
 // weights only, so it runs beside the output projection, LayerNorm and
 // cross-query projection instead of after them.  Where those leave compute
-// units idle (a short sequence: 192 tiles of 256 x 256 on 256 CUs) its tiles
-// fill them.  The mutex covers a call's enqueue from fork to join, so calls
+// units idle (a short sequence: 192 tiles of 128 x 128 at 1,024 x 3,072
+// outputs on 256 CUs) its tiles fill them.  The mutex covers a call's enqueue from fork to join, so calls
 // from several host threads never interleave their use of the two events.
 struct SideStream {
   hipStream_t stream = nullptr;

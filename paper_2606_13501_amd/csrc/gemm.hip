@@ -39,6 +39,10 @@
 // 8.69 -> 8.28 ms (1.44 PFLOP/s); 4,096 x 12,288 x 3,072 (GELU) 257 -> 224
 // us; 4,096 x 3,072 x 12,288 246 -> 210 us; 4,096 x 9,216 x 3,072 189 -> 161
 // us; 1,024 x 3,072 x 3,072 63 -> 27 us; 1,024 x 3,072 x 12,288 171 -> 81 us.
+// These are repeated launches, whose weights come from the caches.  With weights
+// from memory, as in a model whose blocks do not fit the 256 MB last-level
+// cache, few rows take longer: 1,024 x 3,072 x 3,072 66 -> 35 us, x 12,288 193
+// -> 117 us (4,096 rows: within 3% of the times above).
 //
 // fp32 (the small exact configuration): see gemm_f32_nt.
 #include <atomic>
@@ -324,7 +328,9 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_nt(
     // eight columns per lane, so each global access of a wave covers whole
     // 64- or 128-byte row segments with 16 bytes per lane.  The window's 16-byte
     // chunks are permuted (even chunks of a row first) and XOR-swizzled by row
-    // so that writes and reads are free of bank conflicts.  One wave's LDS
+    // against bank conflicts (some are left: the conflict counter reads 0 in the
+    // K loop and a fixed amount per tile, 4.4% of the LDS cycles at K = 5,120
+    // and 1.8% at 13,824).  One wave's LDS
     // operations complete in order, so the window needs no barrier.  The
     // residual rows of a row block pair are loaded one pair ahead.  C may
     // alias R: every element is read before it is written, by the same lane.
@@ -612,8 +618,12 @@ typedef Shape<4, 4, 4, false> Tile128x128;
 // step `step`, plus `full` times the share of the compute units that the round
 // keeps busy (the chip slows down under load, as it runs at its power limit).
 // Fitted to 98 GEMMs of the image and video blocks' projections at 100 to
-// 16,000 rows, each timed with every shape: the shape with the least estimate
-// was the fastest one or within 1% of it in all of them.  With few rows the
+// 16,000 rows, each timed with every shape and weights from the caches: the
+// shape with the least estimate was the fastest one or within 1% of it in all
+// of them.  With weights from memory the launches take longer than the estimate
+// (at 1,024 rows up to 1.45 times), but the choice is still the fastest or
+// within 2% in 30 of 32 shapes at 100 to 5,417 rows (2,048 x 9,216 x 3,072 116
+// us, 109 with 256 x 192; 5,417 x 3,072 x 12,288 384, 372).  With few rows the
 // small tiles use more compute units (1,024 x 3,072 x 3,072: 57 us with 256 x
 // 256, 45 with 256 x 192, 24 with 128 x 128); with many rows a large tile
 // reads each operand less often (16,000 x 12,288 x 3,072: 857, 895 and 1,145
@@ -647,10 +657,14 @@ int choose_tile(int64_t M, int N, int K, int cus) {
 
 // Tile rows per raster group.  A group of G rows lets the 32 tiles resident on
 // an XCD cover G x 32 / G tiles and share their panels in its L2.  Timed with
-// 2, 3, 4, 6, 8 and 16: up to 40 tile rows 6 to 8 are fastest or within 1%
-// (9,216 x 5,120 x 5,120: 340 us with 2, 333 with 8); at 32,760 rows 4 (3.46
-// against 3.51 and 3.52 ms with 2 and 8 on the QKV shape); at 75,600 rows 3
-// (8.29 against 8.33 and 8.61 ms with 4 and 8).
+// 2, 3, 4, 6, 8 and 16 on the image and video blocks' projections at 11 to 296
+// tile rows, of 128 or 256 rows as the shape was chosen: the rule is the fastest
+// or within 1% of it but for a few shapes at 2 to 3% (10,240 x 5,120 x 13,824,
+// 40 tile rows, 1,193 us, 1,155 with 2; 12,800 x 15,360 x 5,120, 50, 1,433, 1,390
+// with 6).  9,216 x 5,120 x 5,120: 340 us with 2, 333 with 8; at 32,760 rows
+// 3.51 ms with 4, 3.58 and 3.63 with 2 and 8 on the QKV shape; at 75,600 rows
+// 8.29 with 3, 8.33 and 8.61 with 4 and 8.  Between 4 and 3 there is no clear
+// line from 100 to 296 tile rows (1% either way).
 int raster(int tiles_m) { return tiles_m <= 40 ? 8 : tiles_m <= 160 ? 4 : 3; }
 
 template <int EPI, typename S>
