@@ -155,3 +155,15 @@ def test_launch_forms(dtype, shape, src, dst, entries):
     else:
         to = _bands(dst[0], shape, dst[1])
     assert _run(M.SHARDED, g, _bands(src[0], shape, src[1]), to) == entries
+
+
+def test_a_box_beyond_32_bit_indices_between_small_ones():
+    """2^31 units and more in one box (1-byte units): a launch of its own, after
+    the boxes before it."""
+    log("case migrate 2 GiB box of 7-byte rows between two small ones")
+    if torch.cuda.mem_get_info()[0] < 20 << 30:
+        pytest.skip("needs 20 GiB of GPU memory")
+    cut = [0, 100, 100 + 2**31 // 7 + 10, 2**31 // 7 + 213]
+    g = torch.randint(0, 255, (cut[-1], 7), device="cuda", dtype=torch.uint8)
+    dst = [(1 + k, [a, 0], [b, 7]) for k, (a, b) in enumerate(zip(cut, cut[1:]))]
+    assert _run(M.SHARDED, g, [(0, [0, 0], [cut[-1], 7])], dst) == 3
